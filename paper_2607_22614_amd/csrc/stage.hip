@@ -17,6 +17,14 @@
 //     destination, contiguous within a row;
 //   * every load of a lane is issued before the first convert (K = 2 or 4
 //     independent 16-byte loads in flight per lane: the plan's tile depth);
+//   * segments that are no whole groups (column slices of an odd width) move
+//     groups of 4 elements too, on the destination's 8-byte grid with 16-byte
+//     loads at 4-byte boundaries.  Bound: as the aligned path, plus the rows'
+//     partial lines.  A 12-layer decoder with 1821-element down slices on 3
+//     ranks (4.05 GB, 27 % of it unaligned) took 693 us with one element per
+//     lane, 4-byte loads and 2-byte stores, and takes 650 us; with the elements
+//     of a group that a row ends in loaded one by one it took 661 us, with 1 or
+//     4 groups per lane instead of 2 679-690 us;
 //   * XCD-aware tile order: the hardware hands workgroup b to XCD b % 8, and
 //     the kernel maps it to a tile so that each XCD streams through one
 //     contiguous eighth of the stream instead of every eighth tile (measured
@@ -86,6 +94,42 @@ __device__ __forceinline__ uint32_t div_cols(uint32_t e, uint32_t cols, uint32_t
   return q;
 }
 
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+constexpr int kGroups = kScalarIters / 4;  // groups of 4 elements per lane in an unaligned tile
+static_assert(kScalarIters % 4 == 0, "unaligned tiles are whole groups per lane");
+
+// A group of an unaligned segment on its way: element j comes from a if j < cut, else from b.
+struct Group {
+  f32x4 a, b;
+  uint32_t cut;
+};
+
+// Loads elements [e, e+4) of an unaligned segment, 0 for those outside [0, units).  A group inside
+// the segment takes one 16-byte load at a 4-byte boundary; if its row ends inside it, a second
+// one brings the rest from the next row (both lie between the group's first and last source
+// element: the row after the cut belongs to the segment).  The segment's ends and rows shorter
+// than a group are loaded element by element, so nothing outside the segment's span is read.
+__device__ __forceinline__ void load_group(const float* __restrict__ src, const DevSeg& s, int32_t e, Group& g) {
+  uint32_t col = (uint32_t)e, row = 0;
+  if (s.rows > 1) row = div_cols((uint32_t)max(e, 0), s.cols, s.magic, &col);
+  g.a = g.b = (f32x4){0.f, 0.f, 0.f, 0.f};
+  g.cut = 4;
+  if (e >= 0 && (uint32_t)e + 4 <= s.units && s.cols >= 4) {
+    const float* p = src + row * s.stride + col;
+    g.a = __builtin_nontemporal_load(reinterpret_cast<const f32x4u*>(p));
+    g.cut = min(s.cols - col, 4u);
+    if (g.cut < 4) g.b = __builtin_nontemporal_load(reinterpret_cast<const f32x4u*>(p + (s.stride - s.cols)));
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (e + j < 0 || (uint32_t)(e + j) >= s.units) continue;
+      uint32_t c = (uint32_t)(e + j), r = 0;
+      if (s.rows > 1) r = div_cols((uint32_t)(e + j), s.cols, s.magic, &c);
+      g.a[j] = load_stream(src + r * s.stride + c);
+    }
+  }
+}
+
 // One workgroup per tile (grid-stride when the grid is capped); K groups of 4
 // elements per lane on aligned segments.
 template <int K>
@@ -100,12 +144,12 @@ __global__ __launch_bounds__(kThreads) void stage_kernel(StageArgs args) {
     const float* __restrict__ src = a.shards[s.shard] + s.src;
     uint16_t* __restrict__ out = a.dst + (s.dst - a.dst_bias);
     // Checksum of the tile: word j of the chunk counts (j+1)*w_j.  With jb the
-    // chunk word index of the segment's first element, j = jb + rel where
-    // rel < 2^31 is the word index relative to the segment, so lanes sum
+    // chunk word index of the segment's first group of 4 elements, j = jb + rel
+    // where rel < 2^31 is the word index relative to that group, so lanes sum
     // A = sum w and R = sum rel*w with 32x32->64 multiply-adds and the tile's
     // s2 = (jb+1)*A + R is formed once at the end.
     const uint64_t pos0 = s.dst - (uint64_t)s.chunk * a.chunk_elems;  // element position in the chunk
-    const uint32_t odd0 = (uint32_t)(pos0 & 1);
+    const uint32_t lead = (uint32_t)(pos0 & 3);  // elements of the first group before the segment (0 if aligned)
     uint64_t acc_w = 0, acc_rw = 0;
     const uint32_t last = s.units - 1;
 
@@ -134,37 +178,62 @@ __global__ __launch_bounds__(kThreads) void stage_kernel(StageArgs args) {
         if (u <= last) {
           const uint32_t e = u * 4;
           store_stream((u32x2){w0, w1}, reinterpret_cast<u32x2*>(out + e));
-          const uint32_t rel = e >> 1;  // pos0 is even on aligned segments
+          const uint32_t rel = e >> 1;
           acc_w += (uint64_t)w0 + w1;
           acc_rw += (uint64_t)rel * w0 + (uint64_t)(rel + 1) * w1;
         }
       }
     } else {
-      // Unaligned segment (runs that are not whole 4-element groups): one
-      // element per lane per step; each element adds its half of a word.
-      float h[kScalarIters];
+      // Unaligned segment (a source offset, destination offset or row that is no whole group of 4
+      // elements).  The tiles still move groups of 4 elements, laid on the destination's 8-byte
+      // grid: group g of the segment holds its elements [4g - lead, 4g - lead + 4), so the
+      // first and the last group can be partial and a row can end inside a group.
+      Group v[kGroups];
 #pragma unroll
-      for (int k = 0; k < kScalarIters; ++k) {
-        const uint32_t e = min(tile.unit0 + k * kThreads + threadIdx.x, last);
-        uint32_t col = e, row = 0;
-        if (s.rows > 1) row = div_cols(e, s.cols, s.magic, &col);
-        h[k] = load_stream(src + row * s.stride + col);
+      for (int k = 0; k < kGroups; ++k) {
+        const int32_t e = (int32_t)(tile.unit0 + 4 * (k * kThreads + threadIdx.x)) - (int32_t)lead;
+        load_group(src, s, e, v[k]);
       }
 #pragma unroll
-      for (int k = 0; k < kScalarIters; ++k) {
-        const uint32_t e = tile.unit0 + k * kThreads + threadIdx.x;
-        const uint32_t bf = cvt_pk_bf16(h[k], 0.f) & 0xFFFFu;
-        if (e <= last) {
-          out[e] = (uint16_t)bf;
-          const uint32_t q = odd0 + e;  // element position relative to the word holding the first element
-          const uint32_t val = bf << ((q & 1) * 16);
-          acc_w += val;
-          acc_rw += (uint64_t)(q >> 1) * val;
+      for (int k = 0; k < kGroups; ++k) {
+        const uint32_t g4 = tile.unit0 + 4 * (k * kThreads + threadIdx.x);  // 4 * group
+        const int32_t e = (int32_t)g4 - (int32_t)lead;
+        f32x4 x = v[k].a;
+        if (v[k].cut < 4) {
+#pragma unroll
+          for (int j = 1; j < 4; ++j) x[j] = (uint32_t)j < v[k].cut ? x[j] : v[k].b[j];
         }
+        const uint32_t w0 = cvt_pk_bf16(x.x, x.y);
+        const uint32_t w1 = cvt_pk_bf16(x.z, x.w);
+        if (e >= 0 && (uint32_t)e + 4 <= s.units) {
+          store_stream((u32x2){w0, w1}, reinterpret_cast<u32x2*>(out + e));
+        } else {
+          const uint16_t h[4] = {(uint16_t)w0, (uint16_t)(w0 >> 16), (uint16_t)w1, (uint16_t)(w1 >> 16)};
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (e + j >= 0 && (uint32_t)(e + j) < s.units) out[e + j] = h[j];
+        }
+        // elements outside the segment were loaded as 0 and add nothing to either sum
+        const uint32_t rel = g4 >> 1;
+        acc_w += (uint64_t)w0 + w1;
+        acc_rw += (uint64_t)rel * w0 + (uint64_t)(rel + 1) * w1;
+      }
+      // The groups of a segment's last tile end `lead` elements before the tile's last unit: up to
+      // three more elements, one lane each.
+      const uint32_t x = tile.unit0 + kScalarUnitsPerTile - lead + threadIdx.x;
+      if (threadIdx.x < lead && tile.unit0 + kScalarUnitsPerTile >= s.units && x < s.units) {
+        uint32_t col = x, row = 0;
+        if (s.rows > 1) row = div_cols(x, s.cols, s.magic, &col);
+        const uint32_t bf = cvt_pk_bf16(load_stream(src + row * s.stride + col), 0.f) & 0xFFFFu;
+        out[x] = (uint16_t)bf;
+        const uint32_t q = lead + x;  // element position relative to the first group
+        const uint32_t val = bf << ((q & 1) * 16);
+        acc_w += val;
+        acc_rw += (uint64_t)(q >> 1) * val;
       }
     }
     block_sum2(acc_w, acc_rw, red);
-    if (threadIdx.x == 0) add_tile_sums(a.sum, a.tile0 + t, s.chunk, acc_w, ((pos0 >> 1) + 1) * acc_w + acc_rw);
+    if (threadIdx.x == 0) add_tile_sums(a.sum, a.tile0 + t, s.chunk, acc_w, (((pos0 - lead) >> 1) + 1) * acc_w + acc_rw);
   }
 }
 
