@@ -300,21 +300,23 @@ int dr_stage_all(dr_plan* plan, const float* const* shards, void* dst, dr_checks
 
 /* The paper's weight path (Sec. 3.3: states go from the old rank to the new
  * one through host memory in bounded chunks, store and reload pipelined chunk
- * by chunk).  The stage kernel packs chunk c straight into one of two
- * plan-owned pinned host buffers of B bytes (its stores cross PCIe), and a
- * plan-owned copy stream reloads that buffer into dst + c*B, so the store of
- * one chunk and the reload of the previous one use both link directions at
- * once.  Transient memory: 2*B pinned, no device staging, allocated on the
- * first call and held by the plan.  Results (dst bytes, d_cks) are identical
- * to dr_stage_all.
+ * by chunk).  Chunk c is packed straight into one of two plan-owned pinned host
+ * buffers of B bytes (the kernel's stores cross PCIe) and reloaded from there
+ * into dst + c*B.  Each launch packs one piece of the stream (a chunk, or about
+ * 32 MiB of a larger one) and reloads the piece before it, so the store of one
+ * and the reload of the other use both link directions at once.  Transient
+ * memory: 2*B pinned, no device staging, allocated on the first call and held
+ * by the plan.  Results (dst bytes, d_cks) are identical to dr_stage_all.
  *   shards, dst, d_cks: as dr_stage_all.  dst may be any device buffer the
- *   current device can copy into.
- *   stream: hipStream_t running the kernels; it also waits for the last copy,
+ *   current device can copy into; one that is not the current device's own
+ *   memory is reloaded by copies on a plan-owned stream.
+ *   stream: hipStream_t running the kernels; it also waits for those copies,
  *   so results are valid once the stream has reached this point.  Does not
  *   block the calling thread.  Calls on one plan are ordered by the plan's
  *   events; the plan must outlive the enqueued work (dr_plan_destroy
- *   synchronizes the copy streams).
- * Errors: DR_EINVAL (as dr_stage_all), DR_ENOMEM, DR_EHIP. */
+ *   synchronizes the device).  Cannot be recorded into a HIP graph.
+ * Errors: DR_EINVAL (as dr_stage_all), DR_ENOMEM, DR_EHIP (the stream is being
+ * captured, among others). */
 int dr_stage_through_host(dr_plan* plan, const float* const* shards, void* dst, dr_checksum* d_cks, void* stream);
 
 /* Training -> training move to a new shard count (Sec. 3.3: weights and
@@ -344,11 +346,10 @@ int dr_reshard(dr_plan* plan, const float* const* src_shards, float* const* dst_
                void* stream);
 
 /* The reshard through host memory, as the paper moves training state from the
- * old ranks to the new ones (Sec. 3.3): the reshard kernel packs destination
- * chunk c straight into one of the plan's two pinned B-byte host buffers, and
- * the plan's copy stream reloads it into the destination shards (cut at shard
- * boundaries), store and reload pipelined chunk by chunk as in
- * dr_stage_through_host.  Transient memory: 2*B pinned, no device staging.
+ * old ranks to the new ones (Sec. 3.3): destination chunk c is packed straight
+ * into one of the plan's two pinned B-byte host buffers and reloaded from there
+ * into the destination shards (cut at shard boundaries), store and reload
+ * pipelined as in dr_stage_through_host.  Transient memory: 2*B pinned, no device staging.
  * Results (every destination byte, d_cks) are identical to dr_reshard.
  *   Arguments, stream semantics, ordering and the one-call-at-a-time rule: as
  *   dr_reshard and dr_stage_through_host.

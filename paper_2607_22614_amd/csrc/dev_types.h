@@ -41,6 +41,15 @@ constexpr uint32_t kScalarUnitsPerTile = kThreads * kScalarIters;  // single ele
 // workgroup visits on that workgroup's XCD.
 constexpr uint32_t kMaxGrid = (0xFFFFFFFFu / kThreads) / kXcds * kXcds;
 
+// Relay launches (pack into pinned host memory and reload, both over the host link): at most this
+// many workgroups, each with kRelayTileBytes in flight each way (more workgroups for smaller
+// tiles).  Too few leave the link idle, too many let the directions drift apart: 48 / 64 / 96 /
+// 128 / 192 workgroups take 28.2 / 27.1 / 26.7 / 27.4 / 31 ms for 0.5B weights in 64 MiB chunks and
+// 61.4 / 60.4 / 60.9 / 62.1 / 64.8 ms for 2.7 GB of training state in 8 MiB chunks.
+constexpr uint32_t kStageRelayGrid = 96;
+constexpr uint32_t kReshardRelayGrid = 64;
+constexpr uint32_t kRelayTileBytes = 8192;
+
 // Segment-table row as the kernels read it (64 bytes, one scalar load).
 // Offsets within a segment fit in 32 bits: the planner keeps rows*cols at most
 // 2^30 and the source span (rows-1)*stride+cols at most 2^31.

@@ -26,6 +26,17 @@ struct StageLaunch {
 };
 hipError_t launch_stage_kernel(const StageLaunch& l, hipStream_t st);
 
+// What a relay launch reloads beside its packing: 16-byte groups from pinned host memory, packed
+// by an earlier launch on the stream, to `to` (stage) or to the destination shards from
+// destination element elem0 on (reshard).
+struct Reload {
+  const void* from;
+  void* to;
+  uint64_t elem0;
+  uint32_t groups;
+};
+hipError_t launch_stage_relay(const StageLaunch& l, const Reload& r, hipStream_t st);
+
 // The checksums of chunks [chunk0, chunk0 + nchunks) from their accumulator
 // slots (written by the tile kernels), which are then set back to zero.
 hipError_t launch_chunk_sums(const ChunkSum& cs, uint32_t chunk0, uint32_t nchunks, hipStream_t st);
@@ -48,5 +59,7 @@ struct ReshardLaunch {
   float* const* dst;
 };
 hipError_t launch_reshard_kernel(const ReshardLaunch& l, hipStream_t st);
+// The same into flat, and the reload r into l.dst.
+hipError_t launch_reshard_relay(const ReshardLaunch& l, const Reload& r, hipStream_t st);
 
 }  // namespace dr

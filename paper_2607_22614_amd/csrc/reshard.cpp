@@ -31,6 +31,20 @@ int check_reshard_args(const dr_plan* p, const float* const* src_shards, float* 
   return DR_OK;
 }
 
+ReshardLaunch reshard_launch(const dr_plan* p, const float* const* src, float* const* dst, const ChunkSum& cs) {
+  ReshardLaunch l{};
+  l.segs = p->d_segs;
+  l.tiles = p->tiling[0].d_tiles;
+  l.sum = cs;
+  l.chunk_elems = p->layout.chunk_bytes / 4;
+  l.dst_shard_elems = p->dst_shard_elems;
+  l.num_src = p->layout.train_shards;
+  l.src = src;
+  l.num_dst = p->dst_shards;
+  l.dst = dst;
+  return l;
+}
+
 namespace {
 
 // Tiles [tile0, tile0 + ntiles) of a reshard plan; flat (if not null) receives the destination
@@ -39,20 +53,11 @@ namespace {
 int launch_reshard(dr_plan* p, uint32_t tile0, uint32_t ntiles, const float* const* src, float* const* dst,
                    float* flat, uint64_t flat_bias, uint32_t chunk0, uint32_t nchunks, dr_checksum* cks,
                    hipStream_t st, const char* what) {
-  ReshardLaunch l{};
-  l.segs = p->d_segs;
-  l.tiles = p->tiling[0].d_tiles;
-  l.sum = chunk_sum(p, p->tiling[0], cks, chunk0);
-  l.chunk_elems = p->layout.chunk_bytes / 4;
-  l.dst_shard_elems = p->dst_shard_elems;
+  ReshardLaunch l = reshard_launch(p, src, dst, chunk_sum(p, p->tiling[0], cks, chunk0));
   l.tile0 = tile0;
   l.ntiles = ntiles;
   l.flat = flat;
   l.flat_bias = flat_bias;
-  l.num_src = p->layout.train_shards;
-  l.src = src;
-  l.num_dst = p->dst_shards;
-  l.dst = dst;
   hipError_t e = launch_reshard_kernel(l, st);
   if (e != hipSuccess) return fail(DR_EHIP, "%s: kernel launch: %s", what, hipGetErrorString(e));
   e = launch_chunk_sums(l.sum, chunk0, nchunks, st);

@@ -29,54 +29,109 @@ struct ReshardArgs {
   float* dst[DR_MAX_SHARDS];
 };
 
+// K groups per lane of tile g, from the tile's unit `first` on: loads, stores and adds the
+// checksum sums.  Every lane of the workgroup calls it.
+template <int K>
+__device__ __forceinline__ void reshard_tile(const ReshardArgs& a, uint32_t g, uint32_t first,
+                                             uint64_t (*red)[kThreads / 64]) {
+  const Tile tile = load_tile(a.tiles, g);
+  const DevSeg s = load_seg(a.segs, tile.seg);
+  const uint32_t unit0 = tile.unit0 + first;
+  if (unit0 >= s.units) return;
+  float* __restrict__ out = a.flat ? a.flat + (s.dst - a.flat_bias)
+                                   : a.dst[s.dst_shard] + (s.dst - (uint64_t)s.dst_shard * a.dst_shard_elems);
+  const uint64_t pos0 = s.dst - (uint64_t)s.chunk * a.chunk_elems;  // word position in the chunk
+  const uint32_t last = s.units - 1;
+  uint64_t acc_w = 0, acc_rw = 0;
+  if (s.op == DR_OP_ZERO_F32) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const uint32_t u = unit0 + k * kThreads + threadIdx.x;
+      if (u <= last) store_stream((f32x4){0.f, 0.f, 0.f, 0.f}, reinterpret_cast<f32x4*>(out + 4 * u));
+    }
+  } else {
+    const float* __restrict__ src = a.src[s.shard] + s.src;
+    u32x4 v[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const uint32_t u = min(unit0 + k * kThreads + threadIdx.x, last);
+      v[k] = load_stream(reinterpret_cast<const u32x4*>(src + 4 * u));
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const uint32_t u = unit0 + k * kThreads + threadIdx.x;
+      if (u <= last) {
+        store_stream(v[k], reinterpret_cast<u32x4*>(out + 4 * u));
+        const uint32_t e = 4 * u;  // word index relative to the segment
+        acc_w += (uint64_t)v[k].x + v[k].y + (uint64_t)v[k].z + v[k].w;
+        acc_rw += (uint64_t)e * v[k].x + (uint64_t)(e + 1) * v[k].y + (uint64_t)(e + 2) * v[k].z +
+                  (uint64_t)(e + 3) * v[k].w;
+      }
+    }
+  }
+  block_sum2(acc_w, acc_rw, red);
+  if (threadIdx.x == 0) add_tile_sums(a.sum, g, s.chunk, acc_w, (pos0 + 1) * acc_w + acc_rw);
+}
+
 __global__ __launch_bounds__(kThreads) void reshard_kernel(ReshardArgs args) {
   (void)args;  // read through the kernarg segment (same bytes)
   const ReshardArgs& a = *(const ReshardArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   __shared__ uint64_t red[2][kThreads / 64];
-  for (uint32_t b = blockIdx.x; b < a.ntiles; b += gridDim.x) {
-    const uint32_t t = xcd_tile(b, a.ntiles);
-    const Tile tile = load_tile(a.tiles, a.tile0 + t);
-    const DevSeg s = load_seg(a.segs, tile.seg);
-    float* __restrict__ out = a.flat ? a.flat + (s.dst - a.flat_bias)
-                                     : a.dst[s.dst_shard] + (s.dst - (uint64_t)s.dst_shard * a.dst_shard_elems);
-    const uint64_t pos0 = s.dst - (uint64_t)s.chunk * a.chunk_elems;  // word position in the chunk
-    const uint32_t last = s.units - 1;
-    uint64_t acc_w = 0, acc_rw = 0;
-    if (s.op == DR_OP_ZERO_F32) {
+  for (uint32_t b = blockIdx.x; b < a.ntiles; b += gridDim.x)
+    reshard_tile<kReshardIters>(a, a.tile0 + xcd_tile(b, a.ntiles), 0, red);
+}
+
+// The path through host memory: packs tiles [tile0, tile0 + ntiles) into pinned host memory (flat)
+// and reloads what the previous launch packed into the destination shards, in alternation
+// (the reason is at the stage kernel's form).  A step is half a tile, 8 KiB each way.  2.7 GB each
+// way in 8 MiB chunks, 5 to 3 shards: 77.5 -> 60.4 ms (a packing kernel and copies before).
+constexpr int kRelayIters = 2;
+constexpr uint32_t kTileSteps = kReshardIters / kRelayIters;
+static_assert(kReshardIters % kRelayIters == 0, "whole steps per tile");
+
+struct ReshardRelayArgs {
+  ReshardArgs s;
+  const u32x4* from;  // pinned, 16-byte groups of the previous launch
+  uint64_t elem0;     // destination element of the first group
+  uint32_t groups;
+  uint32_t shard0;    // destination shard of elem0
+};
+
+__global__ __launch_bounds__(kThreads) void reshard_relay_kernel(ReshardRelayArgs args) {
+  (void)args;  // read through the kernarg segment (same bytes)
+  const ReshardRelayArgs& a = *(const ReshardRelayArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  __shared__ uint64_t red[2][kThreads / 64];
+  constexpr uint32_t per = kThreads * kRelayIters;
+  const uint32_t reloads = (a.groups + per - 1) / per, packs = a.s.ntiles * kTileSteps, steps = max(packs, reloads);
+  const uint64_t S2 = a.s.dst_shard_elems;
+  for (uint32_t b = blockIdx.x; b < steps; b += gridDim.x) {
+    const uint32_t u0 = b * per + threadIdx.x;
+    u32x4 v[kRelayIters];
+    if (b < reloads) {
 #pragma unroll
-      for (int k = 0; k < kReshardIters; ++k) {
-        const uint32_t u = tile.unit0 + k * kThreads + threadIdx.x;
-        if (u <= last) store_stream((f32x4){0.f, 0.f, 0.f, 0.f}, reinterpret_cast<f32x4*>(out + 4 * u));
-      }
-    } else {
-      const float* __restrict__ src = a.src[s.shard] + s.src;
-      u32x4 v[kReshardIters];
+      for (int k = 0; k < kRelayIters; ++k) v[k] = load_stream(a.from + min(u0 + k * kThreads, a.groups - 1));
+    }
+    if (b < packs) reshard_tile<kRelayIters>(a.s, a.s.tile0 + b / kTileSteps, b % kTileSteps * per, red);
+    if (b < reloads) {
 #pragma unroll
-      for (int k = 0; k < kReshardIters; ++k) {
-        const uint32_t u = min(tile.unit0 + k * kThreads + threadIdx.x, last);
-        v[k] = load_stream(reinterpret_cast<const u32x4*>(src + 4 * u));
-      }
-#pragma unroll
-      for (int k = 0; k < kReshardIters; ++k) {
-        const uint32_t u = tile.unit0 + k * kThreads + threadIdx.x;
-        if (u <= last) {
-          store_stream(v[k], reinterpret_cast<u32x4*>(out + 4 * u));
-          const uint32_t e = 4 * u;  // word index relative to the segment
-          acc_w += (uint64_t)v[k].x + v[k].y + (uint64_t)v[k].z + v[k].w;
-          acc_rw += (uint64_t)e * v[k].x + (uint64_t)(e + 1) * v[k].y + (uint64_t)(e + 2) * v[k].z +
-                    (uint64_t)(e + 3) * v[k].w;
+      for (int k = 0; k < kRelayIters; ++k) {
+        const uint32_t u = u0 + k * kThreads;
+        if (u < a.groups) {
+          const uint64_t e = a.elem0 + 4ull * u;
+          uint32_t w = a.shard0;  // at most DR_MAX_SHARDS - 1 steps: e lies in the destination
+          while (e >= (uint64_t)(w + 1) * S2) ++w;
+          store_stream(v[k], reinterpret_cast<u32x4*>(a.s.dst[w] + (e - (uint64_t)w * S2)));
         }
       }
     }
-    block_sum2(acc_w, acc_rw, red);
-    if (threadIdx.x == 0) add_tile_sums(a.sum, a.tile0 + t, s.chunk, acc_w, (pos0 + 1) * acc_w + acc_rw);
   }
 }
 
 }  // namespace
 
-hipError_t launch_reshard_kernel(const ReshardLaunch& l, hipStream_t st) {
-  if (!l.ntiles) return hipSuccess;
+namespace {
+
+ReshardArgs reshard_args(const ReshardLaunch& l) {
   ReshardArgs args;
   std::memset(&args, 0, sizeof(args));
   args.segs = l.segs;
@@ -91,7 +146,30 @@ hipError_t launch_reshard_kernel(const ReshardLaunch& l, hipStream_t st) {
   for (int w = 0; w < l.num_src; ++w) args.src[w] = l.src[w];
   if (l.dst)
     for (int w = 0; w < l.num_dst; ++w) args.dst[w] = l.dst[w];
+  return args;
+}
+
+}  // namespace
+
+hipError_t launch_reshard_kernel(const ReshardLaunch& l, hipStream_t st) {
+  if (!l.ntiles) return hipSuccess;
+  const ReshardArgs args = reshard_args(l);
   hipLaunchKernelGGL(reshard_kernel, dim3(std::min(l.ntiles, kMaxGrid)), dim3(kThreads), 0, st, args);
+  return hipGetLastError();
+}
+
+hipError_t launch_reshard_relay(const ReshardLaunch& l, const Reload& r, hipStream_t st) {
+  if (!l.ntiles && !r.groups) return hipSuccess;
+  ReshardRelayArgs args;
+  args.s = reshard_args(l);
+  args.from = static_cast<const u32x4*>(r.from);
+  args.elem0 = r.elem0;
+  args.groups = r.groups;
+  args.shard0 = (uint32_t)(r.elem0 / l.dst_shard_elems);
+  constexpr uint32_t per = kThreads * kRelayIters;
+  static_assert(16 * per == kRelayTileBytes, "a step moves kRelayTileBytes each way");
+  const uint32_t steps = std::max(l.ntiles * kTileSteps, (r.groups + per - 1) / per);
+  hipLaunchKernelGGL(reshard_relay_kernel, dim3(std::min(steps, kReshardRelayGrid)), dim3(kThreads), 0, st, args);
   return hipGetLastError();
 }
 

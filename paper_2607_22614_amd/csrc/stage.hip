@@ -130,110 +130,152 @@ __device__ __forceinline__ void load_group(const float* __restrict__ src, const 
   }
 }
 
-// One workgroup per tile (grid-stride when the grid is capped); K groups of 4
-// elements per lane on aligned segments.
+// Tile g of the tiling: loads, converts, stores and adds its checksum sums; K groups of 4 elements
+// per lane on aligned segments.  Every lane of the workgroup calls it.
+template <int K>
+__device__ __forceinline__ void stage_tile(const StageArgs& a, uint32_t g, uint64_t (*red)[kThreads / 64]) {
+  const Tile tile = load_tile(a.tiles, g);
+  const DevSeg s = load_seg(a.segs, tile.seg);
+  const float* __restrict__ src = a.shards[s.shard] + s.src;
+  uint16_t* __restrict__ out = a.dst + (s.dst - a.dst_bias);
+  // Checksum of the tile: word j of the chunk counts (j+1)*w_j.  With jb the
+  // chunk word index of the segment's first group of 4 elements, j = jb + rel
+  // where rel < 2^31 is the word index relative to that group, so lanes sum
+  // A = sum w and R = sum rel*w with 32x32->64 multiply-adds and the tile's
+  // s2 = (jb+1)*A + R is formed once at the end.
+  const uint64_t pos0 = s.dst - (uint64_t)s.chunk * a.chunk_elems;  // element position in the chunk
+  const uint32_t lead = (uint32_t)(pos0 & 3);  // elements of the first group before the segment (0 if aligned)
+  uint64_t acc_w = 0, acc_rw = 0;
+  const uint32_t last = s.units - 1;
+
+  if (s.flags & DR_SEG_VEC4) {
+    const bool contiguous = s.rows == 1;
+    f32x4 v[K];
+    // Loads first, all unconditional: lanes past the end of a ragged tile
+    // re-read the segment's last group and store nothing.
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const uint32_t u = min(tile.unit0 + k * kThreads + threadIdx.x, last);
+      const uint32_t e = u * 4;
+      uint32_t so = e;
+      if (!contiguous) {
+        uint32_t col;
+        const uint32_t row = div_cols(e, s.cols, s.magic, &col);
+        so = row * s.stride + col;
+      }
+      v[k] = load_stream(reinterpret_cast<const f32x4*>(src + so));
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const uint32_t u = tile.unit0 + k * kThreads + threadIdx.x;
+      const uint32_t w0 = cvt_pk_bf16(v[k].x, v[k].y);
+      const uint32_t w1 = cvt_pk_bf16(v[k].z, v[k].w);
+      if (u <= last) {
+        const uint32_t e = u * 4;
+        store_stream((u32x2){w0, w1}, reinterpret_cast<u32x2*>(out + e));
+        const uint32_t rel = e >> 1;
+        acc_w += (uint64_t)w0 + w1;
+        acc_rw += (uint64_t)rel * w0 + (uint64_t)(rel + 1) * w1;
+      }
+    }
+  } else {
+    // Unaligned segment (a source offset, destination offset or row that is no whole group of 4
+    // elements).  The tiles still move groups of 4 elements, laid on the destination's 8-byte
+    // grid: group g of the segment holds its elements [4g - lead, 4g - lead + 4), so the
+    // first and the last group can be partial and a row can end inside a group.
+    Group v[kGroups];
+#pragma unroll
+    for (int k = 0; k < kGroups; ++k) {
+      const int32_t e = (int32_t)(tile.unit0 + 4 * (k * kThreads + threadIdx.x)) - (int32_t)lead;
+      load_group(src, s, e, v[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < kGroups; ++k) {
+      const uint32_t g4 = tile.unit0 + 4 * (k * kThreads + threadIdx.x);  // 4 * group
+      const int32_t e = (int32_t)g4 - (int32_t)lead;
+      f32x4 x = v[k].a;
+      if (v[k].cut < 4) {
+#pragma unroll
+        for (int j = 1; j < 4; ++j) x[j] = (uint32_t)j < v[k].cut ? x[j] : v[k].b[j];
+      }
+      const uint32_t w0 = cvt_pk_bf16(x.x, x.y);
+      const uint32_t w1 = cvt_pk_bf16(x.z, x.w);
+      if (e >= 0 && (uint32_t)e + 4 <= s.units) {
+        store_stream((u32x2){w0, w1}, reinterpret_cast<u32x2*>(out + e));
+      } else {
+        const uint16_t h[4] = {(uint16_t)w0, (uint16_t)(w0 >> 16), (uint16_t)w1, (uint16_t)(w1 >> 16)};
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (e + j >= 0 && (uint32_t)(e + j) < s.units) out[e + j] = h[j];
+      }
+      // elements outside the segment were loaded as 0 and add nothing to either sum
+      const uint32_t rel = g4 >> 1;
+      acc_w += (uint64_t)w0 + w1;
+      acc_rw += (uint64_t)rel * w0 + (uint64_t)(rel + 1) * w1;
+    }
+    // The groups of a segment's last tile end `lead` elements before the tile's last unit: up to
+    // three more elements, one lane each.
+    const uint32_t x = tile.unit0 + kScalarUnitsPerTile - lead + threadIdx.x;
+    if (threadIdx.x < lead && tile.unit0 + kScalarUnitsPerTile >= s.units && x < s.units) {
+      uint32_t col = x, row = 0;
+      if (s.rows > 1) row = div_cols(x, s.cols, s.magic, &col);
+      const uint32_t bf = cvt_pk_bf16(load_stream(src + row * s.stride + col), 0.f) & 0xFFFFu;
+      out[x] = (uint16_t)bf;
+      const uint32_t q = lead + x;  // element position relative to the first group
+      const uint32_t val = bf << ((q & 1) * 16);
+      acc_w += val;
+      acc_rw += (uint64_t)(q >> 1) * val;
+    }
+  }
+  block_sum2(acc_w, acc_rw, red);
+  if (threadIdx.x == 0) add_tile_sums(a.sum, g, s.chunk, acc_w, (((pos0 - lead) >> 1) + 1) * acc_w + acc_rw);
+}
+
+// One workgroup per tile (grid-stride when the grid is capped).
 template <int K>
 __global__ __launch_bounds__(kThreads) void stage_kernel(StageArgs args) {
   (void)args;  // read below through the kernarg segment (same bytes)
   const StageArgs& a = *(const StageArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   __shared__ uint64_t red[2][kThreads / 64];
-  for (uint32_t b = blockIdx.x; b < a.ntiles; b += gridDim.x) {
-    const uint32_t t = xcd_tile(b, a.ntiles);
-    const Tile tile = load_tile(a.tiles, a.tile0 + t);
-    const DevSeg s = load_seg(a.segs, tile.seg);
-    const float* __restrict__ src = a.shards[s.shard] + s.src;
-    uint16_t* __restrict__ out = a.dst + (s.dst - a.dst_bias);
-    // Checksum of the tile: word j of the chunk counts (j+1)*w_j.  With jb the
-    // chunk word index of the segment's first group of 4 elements, j = jb + rel
-    // where rel < 2^31 is the word index relative to that group, so lanes sum
-    // A = sum w and R = sum rel*w with 32x32->64 multiply-adds and the tile's
-    // s2 = (jb+1)*A + R is formed once at the end.
-    const uint64_t pos0 = s.dst - (uint64_t)s.chunk * a.chunk_elems;  // element position in the chunk
-    const uint32_t lead = (uint32_t)(pos0 & 3);  // elements of the first group before the segment (0 if aligned)
-    uint64_t acc_w = 0, acc_rw = 0;
-    const uint32_t last = s.units - 1;
+  for (uint32_t b = blockIdx.x; b < a.ntiles; b += gridDim.x)
+    stage_tile<K>(a, a.tile0 + xcd_tile(b, a.ntiles), red);
+}
 
-    if (s.flags & DR_SEG_VEC4) {
-      const bool contiguous = s.rows == 1;
-      f32x4 v[K];
-      // Loads first, all unconditional: lanes past the end of a ragged tile
-      // re-read the segment's last group and store nothing.
+// The path through host memory: packs tiles [tile0, tile0 + ntiles) into pinned host memory (dst)
+// and reloads what the previous launch packed.  Bound by the host link, which moves both
+// directions at once at about 49 GB/s each way as long as both are kept equally busy: each
+// workgroup therefore alternates, K/2 16-byte reload groups per lane (a tile's output bytes)
+// in flight across each tile it packs.  Probe, each way: a packing kernel beside a copy engine's
+// reload 42.5 GB/s for 64 MiB chunks and 32 for 8 MiB (two event waits across queues per
+// chunk); packing and reloading workgroups side by side in one launch 17-46, by their numbers;
+// alternating 47.9 and 45.9.  0.5B weights in 64 MiB chunks 30.1 -> 26.7 ms.
+struct StageRelayArgs {
+  StageArgs s;
+  const u32x4* from;  // pinned, 16-byte groups of the previous launch
+  u32x4* to;
+  uint32_t groups;
+};
+
+template <int K>
+__global__ __launch_bounds__(kThreads) void stage_relay_kernel(StageRelayArgs args) {
+  (void)args;  // read through the kernarg segment (same bytes)
+  const StageRelayArgs& a = *(const StageRelayArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  __shared__ uint64_t red[2][kThreads / 64];
+  constexpr int R = K / 2;
+  const uint32_t reloads = (a.groups + kThreads * R - 1) / (kThreads * R), steps = max(a.s.ntiles, reloads);
+  for (uint32_t b = blockIdx.x; b < steps; b += gridDim.x) {
+    const uint32_t u0 = b * (kThreads * R) + threadIdx.x;
+    u32x4 v[R];
+    if (b < reloads) {
 #pragma unroll
-      for (int k = 0; k < K; ++k) {
-        const uint32_t u = min(tile.unit0 + k * kThreads + threadIdx.x, last);
-        const uint32_t e = u * 4;
-        uint32_t so = e;
-        if (!contiguous) {
-          uint32_t col;
-          const uint32_t row = div_cols(e, s.cols, s.magic, &col);
-          so = row * s.stride + col;
-        }
-        v[k] = load_stream(reinterpret_cast<const f32x4*>(src + so));
-      }
-#pragma unroll
-      for (int k = 0; k < K; ++k) {
-        const uint32_t u = tile.unit0 + k * kThreads + threadIdx.x;
-        const uint32_t w0 = cvt_pk_bf16(v[k].x, v[k].y);
-        const uint32_t w1 = cvt_pk_bf16(v[k].z, v[k].w);
-        if (u <= last) {
-          const uint32_t e = u * 4;
-          store_stream((u32x2){w0, w1}, reinterpret_cast<u32x2*>(out + e));
-          const uint32_t rel = e >> 1;
-          acc_w += (uint64_t)w0 + w1;
-          acc_rw += (uint64_t)rel * w0 + (uint64_t)(rel + 1) * w1;
-        }
-      }
-    } else {
-      // Unaligned segment (a source offset, destination offset or row that is no whole group of 4
-      // elements).  The tiles still move groups of 4 elements, laid on the destination's 8-byte
-      // grid: group g of the segment holds its elements [4g - lead, 4g - lead + 4), so the
-      // first and the last group can be partial and a row can end inside a group.
-      Group v[kGroups];
-#pragma unroll
-      for (int k = 0; k < kGroups; ++k) {
-        const int32_t e = (int32_t)(tile.unit0 + 4 * (k * kThreads + threadIdx.x)) - (int32_t)lead;
-        load_group(src, s, e, v[k]);
-      }
-#pragma unroll
-      for (int k = 0; k < kGroups; ++k) {
-        const uint32_t g4 = tile.unit0 + 4 * (k * kThreads + threadIdx.x);  // 4 * group
-        const int32_t e = (int32_t)g4 - (int32_t)lead;
-        f32x4 x = v[k].a;
-        if (v[k].cut < 4) {
-#pragma unroll
-          for (int j = 1; j < 4; ++j) x[j] = (uint32_t)j < v[k].cut ? x[j] : v[k].b[j];
-        }
-        const uint32_t w0 = cvt_pk_bf16(x.x, x.y);
-        const uint32_t w1 = cvt_pk_bf16(x.z, x.w);
-        if (e >= 0 && (uint32_t)e + 4 <= s.units) {
-          store_stream((u32x2){w0, w1}, reinterpret_cast<u32x2*>(out + e));
-        } else {
-          const uint16_t h[4] = {(uint16_t)w0, (uint16_t)(w0 >> 16), (uint16_t)w1, (uint16_t)(w1 >> 16)};
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if (e + j >= 0 && (uint32_t)(e + j) < s.units) out[e + j] = h[j];
-        }
-        // elements outside the segment were loaded as 0 and add nothing to either sum
-        const uint32_t rel = g4 >> 1;
-        acc_w += (uint64_t)w0 + w1;
-        acc_rw += (uint64_t)rel * w0 + (uint64_t)(rel + 1) * w1;
-      }
-      // The groups of a segment's last tile end `lead` elements before the tile's last unit: up to
-      // three more elements, one lane each.
-      const uint32_t x = tile.unit0 + kScalarUnitsPerTile - lead + threadIdx.x;
-      if (threadIdx.x < lead && tile.unit0 + kScalarUnitsPerTile >= s.units && x < s.units) {
-        uint32_t col = x, row = 0;
-        if (s.rows > 1) row = div_cols(x, s.cols, s.magic, &col);
-        const uint32_t bf = cvt_pk_bf16(load_stream(src + row * s.stride + col), 0.f) & 0xFFFFu;
-        out[x] = (uint16_t)bf;
-        const uint32_t q = lead + x;  // element position relative to the first group
-        const uint32_t val = bf << ((q & 1) * 16);
-        acc_w += val;
-        acc_rw += (uint64_t)(q >> 1) * val;
-      }
+      for (int k = 0; k < R; ++k) v[k] = load_stream(a.from + min(u0 + k * kThreads, a.groups - 1));
     }
-    block_sum2(acc_w, acc_rw, red);
-    if (threadIdx.x == 0) add_tile_sums(a.sum, a.tile0 + t, s.chunk, acc_w, (((pos0 - lead) >> 1) + 1) * acc_w + acc_rw);
+    if (b < a.s.ntiles) stage_tile<K>(a.s, a.s.tile0 + b, red);
+    if (b < reloads) {
+#pragma unroll
+      for (int k = 0; k < R; ++k)
+        if (u0 + k * kThreads < a.groups) store_stream(v[k], a.to + u0 + k * kThreads);
+    }
   }
 }
 
@@ -307,8 +349,9 @@ hipError_t launch_chunk_sums(const ChunkSum& cs, uint32_t chunk0, uint32_t nchun
   return hipGetLastError();
 }
 
-hipError_t launch_stage_kernel(const StageLaunch& l, hipStream_t st) {
-  if (!l.ntiles) return hipSuccess;
+namespace {
+
+StageArgs stage_args(const StageLaunch& l) {
   StageArgs args;
   std::memset(&args, 0, sizeof(args));
   args.segs = l.segs;
@@ -320,12 +363,36 @@ hipError_t launch_stage_kernel(const StageLaunch& l, hipStream_t st) {
   args.tile0 = l.tile0;
   args.ntiles = l.ntiles;
   for (int w = 0; w < l.num_shards; ++w) args.shards[w] = l.shards[w];
+  return args;
+}
+
+}  // namespace
+
+hipError_t launch_stage_kernel(const StageLaunch& l, hipStream_t st) {
+  if (!l.ntiles) return hipSuccess;
+  const StageArgs args = stage_args(l);
   const uint32_t cap = DR_GRID_CAP > 0 ? (uint32_t)DR_GRID_CAP : kMaxGrid;
   const uint32_t grid = l.ntiles < cap ? l.ntiles : cap;
   if (l.depth == kVecItersLarge)
     hipLaunchKernelGGL(stage_kernel<kVecItersLarge>, dim3(grid), dim3(kThreads), 0, st, args);
   else
     hipLaunchKernelGGL(stage_kernel<kVecItersSmall>, dim3(grid), dim3(kThreads), 0, st, args);
+  return hipGetLastError();
+}
+
+hipError_t launch_stage_relay(const StageLaunch& l, const Reload& r, hipStream_t st) {
+  if (!l.ntiles && !r.groups) return hipSuccess;
+  StageRelayArgs args;
+  args.s = stage_args(l);
+  args.from = static_cast<const u32x4*>(r.from);
+  args.to = static_cast<u32x4*>(r.to);
+  args.groups = r.groups;
+  const uint32_t per = kThreads * (l.depth / 2), steps = std::max(l.ntiles, (r.groups + per - 1) / per);
+  const uint32_t grid = std::min(steps, kRelayTileBytes / (16 * per) * kStageRelayGrid);
+  if (l.depth == kVecItersLarge)
+    hipLaunchKernelGGL(stage_relay_kernel<kVecItersLarge>, dim3(grid), dim3(kThreads), 0, st, args);
+  else
+    hipLaunchKernelGGL(stage_relay_kernel<kVecItersSmall>, dim3(grid), dim3(kThreads), 0, st, args);
   return hipGetLastError();
 }
 

@@ -65,18 +65,11 @@ void note_pack(const dr_plan* p, uint64_t bytes) {
 int launch(dr_plan* p, const Tiling& tl, uint32_t tile0, uint32_t ntiles, const float* const* shards, void* dst,
            uint64_t dst_bias, uint32_t chunk0, uint32_t nchunks, const ChunkSum& cs, hipStream_t st,
            const char* what) {
-  StageLaunch l{};
-  l.segs = p->d_segs;
-  l.tiles = tl.d_tiles;
-  l.sum = cs;
+  StageLaunch l = stage_launch(p, tl, shards, cs);
   l.dst = dst;
   l.dst_bias = dst_bias;
-  l.chunk_elems = p->layout.chunk_bytes / 2;
   l.tile0 = tile0;
   l.ntiles = ntiles;
-  l.depth = tl.depth;
-  l.num_shards = p->layout.train_shards;
-  l.shards = shards;
   hipError_t e = launch_stage_kernel(l, st);
   if (e != hipSuccess) return fail(DR_EHIP, "%s: stage kernel launch: %s", what, hipGetErrorString(e));
   p->last_depth.store(tl.depth, std::memory_order_relaxed);
@@ -127,6 +120,18 @@ ChunkSum chunk_sum(const dr_plan* p, const Tiling& tl, dr_checksum* out, uint32_
   cs.out_chunk0 = out_chunk0;
   cs.chunk_bias = 0;
   return cs;
+}
+
+StageLaunch stage_launch(const dr_plan* p, const Tiling& tl, const float* const* shards, const ChunkSum& cs) {
+  StageLaunch l{};
+  l.segs = p->d_segs;
+  l.tiles = tl.d_tiles;
+  l.sum = cs;
+  l.chunk_elems = p->layout.chunk_bytes / 2;
+  l.depth = tl.depth;
+  l.num_shards = p->layout.train_shards;
+  l.shards = shards;
+  return l;
 }
 
 int check_stage_args(const dr_plan* p, const float* const* shards, const void* dst, const void* cks,
