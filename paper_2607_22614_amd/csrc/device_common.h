@@ -111,4 +111,15 @@ __device__ __forceinline__ uint32_t xcd_tile(uint32_t b, uint32_t n) {
   return x * per + min(x, rem) + b / kXcds;
 }
 
+// Item run by the b-th workgroup in grouped order: the XCDs take groups of G consecutive items in
+// turn, so the chip works on one window of 8*G items; the last n % (8*G) items in plain order.  A
+// bijection on [0, n) for every n; item b of a full window runs on XCD b % 8.
+template <uint32_t G, typename T>
+__device__ __forceinline__ T xcd_group(T b, T n) {
+  static_assert((G & (G - 1)) == 0, "power of two");
+  if (b >= (n & ~(T)(kXcds * G - 1))) return b;
+  const T x = b % kXcds, i = b / kXcds;
+  return (i / G * kXcds + x) * G + i % G;
+}
+
 }  // namespace dr

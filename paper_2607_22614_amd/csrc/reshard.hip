@@ -1,8 +1,8 @@
 // Reshard kernel: the training -> training move to a new shard count
 // (weights and optimizer states from the old training ranks to the new ones).
 // The N elements keep their order and bits; they are re-cut into W' shards and
-// the destination padding is zeroed.  Same tiling, XCD order and checksum
-// scheme as the stage kernel, with one fp32 word per element: a lane moves a
+// the destination padding is zeroed.  Same tiling and checksum scheme as the
+// stage kernel, with one fp32 word per element: a lane moves a
 // 16-byte group (one nontemporal load, one nontemporal store).  HBM-bound: 4 B
 // read and 4 B written per element (padding: written only).
 #include <hip/hip_runtime.h>
@@ -16,6 +16,8 @@
 namespace dr {
 namespace {
 
+constexpr uint32_t kPartGroup = 64;
+
 struct ReshardArgs {
   const DevSeg* segs;
   const Tile* tiles;
@@ -23,6 +25,7 @@ struct ReshardArgs {
   uint64_t chunk_elems;      // B / 4
   uint64_t dst_shard_elems;  // S'
   uint32_t tile0, ntiles;
+  uint32_t part_shift;       // log2 of the parts that a workgroup each moves of a tile (reshard_kernel)
   float* flat;               // non-null: write destination element e to flat[e - flat_bias] (one chunk)
   uint64_t flat_bias;
   const float* src[DR_MAX_SHARDS];
@@ -73,12 +76,24 @@ __device__ __forceinline__ void reshard_tile(const ReshardArgs& a, uint32_t g, u
   if (threadIdx.x == 0) add_tile_sums(a.sum, g, s.chunk, acc_w, (pos0 + 1) * acc_w + acc_rw);
 }
 
+// A workgroup moves one part of a tile, one 16-byte group per lane, and the XCDs take groups of 64
+// parts (256 KiB) in turn.  Bound by HBM, where the read and the write stream meet in the same
+// banks: how they fall together depends on the tile's size, on the order and on where the
+// buffers lie.  The 8B shape at 16 layers, 8 to 6 shards (36.3 GB): whole tiles per workgroup,
+// each XCD on its own eighth of the stream 5.65-5.92 ms by process; halves in that order
+// 5.69-6.03, quarters 5.63, quarters in groups of 16 / 64 / 256: 5.90 / 5.56 / 5.62.  At 32 layers
+// 9.64-10.51 against 9.86-9.97 (64); 0.5B 0.830 against 0.777; 5 to 3 shards of an odd width
+// 0.939 against 0.842.
 __global__ __launch_bounds__(kThreads) void reshard_kernel(ReshardArgs args) {
   (void)args;  // read through the kernarg segment (same bytes)
   const ReshardArgs& a = *(const ReshardArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   __shared__ uint64_t red[2][kThreads / 64];
-  for (uint32_t b = blockIdx.x; b < a.ntiles; b += gridDim.x)
-    reshard_tile<kReshardIters>(a, a.tile0 + xcd_tile(b, a.ntiles), 0, red);
+  const uint64_t n = (uint64_t)a.ntiles << a.part_shift;
+  for (uint64_t b = blockIdx.x; b < n; b += gridDim.x) {
+    const uint64_t t = xcd_group<kPartGroup>(b, n);
+    const uint32_t part = (uint32_t)t & ((1u << a.part_shift) - 1);
+    reshard_tile<1>(a, a.tile0 + (uint32_t)(t >> a.part_shift), part * kThreads, red);
+  }
 }
 
 // The path through host memory: packs tiles [tile0, tile0 + ntiles) into pinned host memory (flat)
@@ -153,8 +168,14 @@ ReshardArgs reshard_args(const ReshardLaunch& l) {
 
 hipError_t launch_reshard_kernel(const ReshardLaunch& l, hipStream_t st) {
   if (!l.ntiles) return hipSuccess;
-  const ReshardArgs args = reshard_args(l);
-  hipLaunchKernelGGL(reshard_kernel, dim3(std::min(l.ntiles, kMaxGrid)), dim3(kThreads), 0, st, args);
+  ReshardArgs args = reshard_args(l);
+  // as many parts of kThreads groups as the largest tile has: fewer than kReshardIters where a
+  // chunk is smaller than a tile
+  static_assert(kReshardIters == 4, "tiles of up to 4 parts");
+  const uint64_t groups = l.chunk_elems / 4;
+  args.part_shift = groups <= (uint64_t)kThreads ? 0 : groups <= 2ull * kThreads ? 1 : 2;
+  const uint64_t grid = std::min<uint64_t>((uint64_t)l.ntiles << args.part_shift, kMaxGrid);
+  hipLaunchKernelGGL(reshard_kernel, dim3((uint32_t)grid), dim3(kThreads), 0, st, args);
   return hipGetLastError();
 }
 

@@ -1,0 +1,39 @@
+"""Reshard where its workgroups' parts of a tile and their grouped order can go wrong, on the GPU against the oracle:
+chunks of one group, of one, two and four parts and one group around each, and counts of parts around a window of
+512; ragged shards whose segments end in any part."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2607_22614_amd import datagen, dr
+from tests.gpu_helpers import checksums_to_list, new_checksums, require_gpu, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    require_gpu()
+
+
+@pytest.mark.parametrize("w,w2", [(1, 3), (5, 2)])
+@pytest.mark.parametrize("b", [16, 4080, 4096, 4112, 8176, 8192, 8208, 16368, 16384, 16400, 512 * 4096, 513 * 4096 + 16])
+def test_parts_and_order(b, w, w2):
+    model = (1, 64, 2, 2, 8, 96, 40) if b == 16 else (1, 256, 4, 4, 64, 688, 1000 + (b // 16) % 7)
+    say("reshard parts", model, w, "->", w2, "B", b)
+    plan = dr.dr_reshard_plan_create(model, w, w2, b)
+    info = dr.dr_plan_get_info(plan)
+    flat = datagen.make_flat_numpy(model, w, seed=3, specials_frac=0.01)
+    S, S2 = info["shard_elems"], info["dst_shard_elems"]
+    n = datagen.flat_sizes(model, w)[0]
+    src = [torch.from_numpy(flat[i * S:(i + 1) * S].copy()).cuda() for i in range(w)]
+    want = oracle.reshard(flat, n, w2).view(np.uint32)
+    for _ in range(2):  # the accumulators are back at zero after the first
+        dst = [torch.full((S2,), -1, dtype=torch.int32, device="cuda") for _ in range(w2)]
+        cks = new_checksums(info["num_chunks"])
+        dr.dr_reshard(plan, src, dst, cks)
+        torch.cuda.synchronize()
+        got = np.concatenate([d.cpu().numpy().view(np.uint32) for d in dst])
+        assert np.array_equal(got, want)
+        assert checksums_to_list(cks) == oracle.chunk_checksums(want, b)
