@@ -20,6 +20,7 @@ struct StageLaunch {
   uint64_t dst_bias;
   uint64_t chunk_elems;  // B / 2
   uint32_t tile0, ntiles;
+  bool grouped;  // the XCDs take groups of tiles in turn instead of a contiguous eighth each
   int depth;
   int num_shards;
   const float* const* shards;  // host array of num_shards device pointers

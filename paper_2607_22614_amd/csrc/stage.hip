@@ -28,7 +28,8 @@
 //   * XCD-aware tile order: the hardware hands workgroup b to XCD b % 8, and
 //     the kernel maps it to a tile so that each XCD streams through one
 //     contiguous eighth of the stream instead of every eighth tile (measured
-//     faster on the 8B shape: 6.3 vs 6.0 TB/s);
+//     faster on the 8B shape: 6.3 vs 6.0 TB/s), or, in short launches, so that
+//     the XCDs take groups of 64 tiles in turn (StageLaunch::grouped);
 //   * the chunk checksum is accumulated from the packed words while they are
 //     in registers, reduced across the wavefront (DPP moves, no LDS) and the
 //     workgroup (LDS), and added with two 64-bit atomic adds (nothing waits
@@ -47,6 +48,8 @@
 namespace dr {
 namespace {
 
+constexpr uint32_t kTileGroup = 64;  // tiles of a group in grouped order
+
 // Everything a stage launch needs, passed as the kernel's only argument.  The
 // kernel reads it through the kernarg segment pointer, so the shard table is
 // indexed with one scalar load instead of being copied into registers.
@@ -58,6 +61,7 @@ struct StageArgs {
   uint64_t dst_bias;
   uint64_t chunk_elems;   // B / 2
   uint32_t tile0, ntiles; // tiles [tile0, tile0 + ntiles)
+  uint32_t grouped;       // 1: XCDs take groups of tiles in turn, 0: a contiguous eighth each
   const float* shards[DR_MAX_SHARDS];
 };
 
@@ -238,7 +242,7 @@ __global__ __launch_bounds__(kThreads) void stage_kernel(StageArgs args) {
   const StageArgs& a = *(const StageArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   __shared__ uint64_t red[2][kThreads / 64];
   for (uint32_t b = blockIdx.x; b < a.ntiles; b += gridDim.x)
-    stage_tile<K>(a, a.tile0 + xcd_tile(b, a.ntiles), red);
+    stage_tile<K>(a, a.tile0 + (a.grouped ? xcd_group<kTileGroup>(b, a.ntiles) : xcd_tile(b, a.ntiles)), red);
 }
 
 // The path through host memory: packs tiles [tile0, tile0 + ntiles) into pinned host memory (dst)
@@ -362,6 +366,7 @@ StageArgs stage_args(const StageLaunch& l) {
   args.chunk_elems = l.chunk_elems;
   args.tile0 = l.tile0;
   args.ntiles = l.ntiles;
+  args.grouped = l.grouped;
   for (int w = 0; w < l.num_shards; ++w) args.shards[w] = l.shards[w];
   return args;
 }

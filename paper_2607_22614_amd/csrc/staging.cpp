@@ -30,6 +30,17 @@ int check_device(const dr_plan* p, const char* what) {
   return DR_OK;
 }
 
+// Tile order of a launch.  A short launch is mostly its start, when nothing of source, destination
+// and tables has been touched for a while: in grouped order the chip works on one window of 512
+// tiles, in contiguous order on eight places of the stream at once.  Once the launch runs, contiguous
+// order is the faster one.  One-chunk launches (measured on loops of them) take grouped order: 64
+// MiB chunks of 0.5B 732 -> 686 us for 20 calls, 256 MiB chunks of 8B 7.82 -> 7.71 ms for 60
+// (groups of 4-32 and 128-256 tiles: 686-732 us, 7.82-8.09 ms).  So does a lone pack (deep
+// tiling) up to kGroupedLoneBytes: 0.5 / 1.8 / 3.8 GB moved after 30 ms idle 218 / 379 / 638 us contiguous,
+// 203 / 355 / 635 grouped, but 16 / 48 GB 2.73 / 7.55 ms against 2.78 / 7.66.  Packs behind packs stay
+// contiguous: 0.27 / 0.57 / 7.31 ms against 0.28 / 0.58 / 7.46.
+constexpr uint64_t kGroupedLoneBytes = 4ull << 30;
+
 // Per-device state of the automatic tile depth (see pack_drain_ns in the
 // internal header): when the packs launched so far should have drained.
 std::atomic<int64_t> g_packs_drain_ns[kClockDevices];
@@ -63,13 +74,14 @@ void note_pack(const dr_plan* p, uint64_t bytes) {
 // Tiles [tile0, tile0 + ntiles) of tiling tl, which cover chunks [chunk0, chunk0 + nchunks), then
 // their checksums from the accumulators of cs.
 int launch(dr_plan* p, const Tiling& tl, uint32_t tile0, uint32_t ntiles, const float* const* shards, void* dst,
-           uint64_t dst_bias, uint32_t chunk0, uint32_t nchunks, const ChunkSum& cs, hipStream_t st,
+           uint64_t dst_bias, uint32_t chunk0, uint32_t nchunks, bool grouped, const ChunkSum& cs, hipStream_t st,
            const char* what) {
   StageLaunch l = stage_launch(p, tl, shards, cs);
   l.dst = dst;
   l.dst_bias = dst_bias;
   l.tile0 = tile0;
   l.ntiles = ntiles;
+  l.grouped = grouped;
   hipError_t e = launch_stage_kernel(l, st);
   if (e != hipSuccess) return fail(DR_EHIP, "%s: stage kernel launch: %s", what, hipGetErrorString(e));
   p->last_depth.store(tl.depth, std::memory_order_relaxed);
@@ -146,8 +158,8 @@ int check_stage_args(const dr_plan* p, const float* const* shards, const void* d
 int launch_chunk_into(dr_plan* p, const Tiling& tl, uint64_t chunk, const float* const* shards, void* dst_chunk,
                       const ChunkSum& cs, hipStream_t st, const char* what) {
   const uint32_t t0 = tl.chunk_tile_begin[chunk], t1 = tl.chunk_tile_begin[chunk + 1];
-  return launch(p, tl, t0, t1 - t0, shards, dst_chunk, chunk * (p->layout.chunk_bytes / 2), (uint32_t)chunk, 1, cs,
-                st, what);
+  return launch(p, tl, t0, t1 - t0, shards, dst_chunk, chunk * (p->layout.chunk_bytes / 2), (uint32_t)chunk, 1, true,
+                cs, st, what);
 }
 
 const Tiling& chunk_launch_tiling(const dr_plan* p) { return p->tiling[chunk_tiling(p)]; }
@@ -235,9 +247,12 @@ extern "C" int dr_stage_all(dr_plan* p, const float* const* shards, void* dst, d
   if (!aligned16(d_cks)) return fail(DR_EINVAL, "dr_stage_all: d_cks is null or not 16-byte aligned");
   if (!p->d_segs) return fail(DR_EINVAL, "dr_stage_all: host-only plan has no device tables");
   if (int rc = check_device(p, "dr_stage_all")) return rc;
-  const Tiling& tl = p->tiling[pick_tiling(p)];
+  const int pick = pick_tiling(p);
+  const Tiling& tl = p->tiling[pick];
+  const uint64_t bytes = 4 * p->info.n_elems + p->info.rollout_bytes;
   const int rc = launch(p, tl, 0, (uint32_t)tl.tiles.size(), shards, dst, 0, 0, (uint32_t)p->info.num_chunks,
-                        chunk_sum(p, tl, d_cks, 0), static_cast<hipStream_t>(stream), "dr_stage_all");
-  if (rc == DR_OK) note_pack(p, 4 * p->info.n_elems + p->info.rollout_bytes);
+                        pick == 1 && bytes <= kGroupedLoneBytes, chunk_sum(p, tl, d_cks, 0),
+                        static_cast<hipStream_t>(stream), "dr_stage_all");
+  if (rc == DR_OK) note_pack(p, bytes);
   return rc;
 }
