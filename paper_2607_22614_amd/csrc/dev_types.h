@@ -84,8 +84,11 @@ struct Tile {
 // slots, and how far apart, is the host's choice (a plan's tiling): adds to
 // one cache line are performed one after another, so the slots spread the
 // adds of a chunk's concurrent tiles over lines.
+// A small launch sums its chunks itself instead (ChunkSum::chunk_tiles set): behind its adds each
+// tile takes a ticket of its chunk, and the one with the last ticket does the small kernel's work.
 constexpr uint32_t kMaxSumSlots = 256;
 constexpr uint32_t kSlotLineWords = 16;  // 128-byte line
+constexpr uint32_t kTicketWord = 2;      // of a chunk's first slot, where slots lie a line apart
 
 struct ChunkSum {
   uint64_t* acc;         // (s1, s2) accumulators
@@ -94,6 +97,7 @@ struct ChunkSum {
   uint32_t stride_words; // 64-bit words between consecutive slots (2 or kSlotLineWords)
   uint32_t out_chunk0;
   uint32_t chunk_bias;
+  const uint32_t* chunk_tiles;  // the tiling's chunk -> first tile index, in a launch that sums its chunks itself
 };
 
 }  // namespace dr

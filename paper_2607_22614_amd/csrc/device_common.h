@@ -103,6 +103,37 @@ __device__ __forceinline__ void add_tile_sums(const ChunkSum& cs, uint32_t g, ui
   atomicAdd(p + 1, (unsigned long long)s2);
 }
 
+// The first wave's lanes call it with tile g's (s1, s2) in lane 0, in a launch that sums its chunks
+// itself: adds them like add_tile_sums and takes the tile's ticket, the last of which writes
+// the chunk's checksum and leaves the slots at zero for the next launch, as the ticket is.
+//   The sums are added before the ticket is taken: the adds return their old values and the ticket
+// waits for them, and all of these are atomics on the device's memory, so the wave with the last
+// ticket finds every tile's adds in the slots.  Nothing spins; a launch's tiles each take one
+// ticket.
+__device__ __forceinline__ void finish_tile_sums(const ChunkSum& cs, uint32_t g, uint32_t c, uint64_t s1, uint64_t s2) {
+  const uint32_t lane = threadIdx.x;
+  typedef unsigned long long u64;
+  u64* acc = reinterpret_cast<u64*>(cs.acc) + (uint64_t)(c - cs.chunk_bias) * cs.sub * kSlotLineWords;
+  const uint32_t tiles = cs.chunk_tiles[c + 1] - cs.chunk_tiles[c];
+  uint32_t is_last = 0;
+  if (lane == 0) {
+    u64* p = acc + (g & (cs.sub - 1)) * kSlotLineWords;
+    u64 o1 = atomicAdd(p, (u64)s1), o2 = atomicAdd(p + 1, (u64)s2);
+    asm volatile("" : "+v"(o1), "+v"(o2)::"memory");  // both have returned
+    // counts 0 .. tiles-1 and wraps to 0 by itself
+    is_last = atomicInc(reinterpret_cast<uint32_t*>(acc + kTicketWord), tiles - 1) == tiles - 1;
+  }
+  if (!__builtin_amdgcn_readfirstlane(is_last)) return;
+  uint64_t a1 = 0, a2 = 0;
+  if (lane < cs.sub) {
+    a1 = atomicExch(acc + lane * kSlotLineWords, 0ull);
+    a2 = atomicExch(acc + lane * kSlotLineWords + 1, 0ull);
+  }
+  a1 = wave_sum_to_lane63(a1);
+  a2 = wave_sum_to_lane63(a2);
+  if (lane == 63) *reinterpret_cast<u64x2*>(&cs.out[c - cs.out_chunk0]) = (u64x2){a1, a2};
+}
+
 // Tile run by the b-th workgroup: XCD x = b % 8 takes tiles
 // [x*per + min(x, rem), ...) in order, where per/rem split n tiles over 8
 // XCDs.  A bijection on [0, n) for every n.

@@ -69,6 +69,17 @@ inline uint32_t sum_stride(uint32_t slots, uint32_t max_chunk_tiles) {
   return slots > 1 || max_chunk_tiles > kPackedSlotTiles ? kSlotLineWords : 2;
 }
 
+// Stage launches whose chunks have at most kOwnSumChunkTiles tiles, and that have at most kOwnSumTiles
+// in all, sum their chunks themselves (finish_tile_sums) unless they are recorded into a graph: such
+// a launch is over before the host has enqueued the next one, and a second kernel costs the
+// host 2.7 us.  Through the binding, tiny workload: 13.3 -> 10.1 us a pack, 13.3 -> 10.0 a chunk call.
+// Replayed from a graph only the device counts, where the two are alike up to 64 tiles a chunk (4.3 us
+// against 4.5-4.6 for a 256 KiB chunk) and the tickets of a chunk, taken one after another, cost more
+// than the kernel beyond (1 MiB, 128 tiles: 5.6 against 4.9; 4 MiB: 10.7 against 6.0).  2048: the
+// workgroups that the 256 CUs hold at once; a waiting one would keep others from starting.
+constexpr uint32_t kOwnSumTiles = 2048;
+constexpr uint32_t kOwnSumChunkTiles = 128;
+
 enum PlanKind : int { kRollout = 0, kReshard = 1 };
 
 // One tiling of a plan's segments at tile depth K: the tiles in segment order

@@ -61,6 +61,7 @@ struct StageArgs {
   uint64_t dst_bias;
   uint64_t chunk_elems;   // B / 2
   uint32_t tile0, ntiles; // tiles [tile0, tile0 + ntiles)
+  uint32_t grid;          // workgroups of the launch, at most ntiles
   uint32_t grouped;       // 1: XCDs take groups of tiles in turn, 0: a contiguous eighth each
   const float* shards[DR_MAX_SHARDS];
 };
@@ -135,8 +136,9 @@ __device__ __forceinline__ void load_group(const float* __restrict__ src, const 
 }
 
 // Tile g of the tiling: loads, converts, stores and adds its checksum sums; K groups of 4 elements
-// per lane on aligned segments.  Every lane of the workgroup calls it.
-template <int K>
+// per lane on aligned segments; kOwnSums: in a launch that sums its chunks itself.  Every lane of the
+// workgroup calls it.
+template <int K, bool kOwnSums>
 __device__ __forceinline__ void stage_tile(const StageArgs& a, uint32_t g, uint64_t (*red)[kThreads / 64]) {
   const Tile tile = load_tile(a.tiles, g);
   const DevSeg s = load_seg(a.segs, tile.seg);
@@ -152,7 +154,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, uint32_t g, uint6
   uint64_t acc_w = 0, acc_rw = 0;
   const uint32_t last = s.units - 1;
 
-  if (s.flags & DR_SEG_VEC4) {
+  if (__builtin_expect((s.flags & DR_SEG_VEC4) != 0, 1)) {
     const bool contiguous = s.rows == 1;
     f32x4 v[K];
     // Loads first, all unconditional: lanes past the end of a ragged tile
@@ -232,17 +234,27 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, uint32_t g, uint6
     }
   }
   block_sum2(acc_w, acc_rw, red);
-  if (threadIdx.x == 0) add_tile_sums(a.sum, g, s.chunk, acc_w, (((pos0 - lead) >> 1) + 1) * acc_w + acc_rw);
+  const uint64_t s2 = (((pos0 - lead) >> 1) + 1) * acc_w + acc_rw;
+  if (kOwnSums) {
+    if (threadIdx.x < 64) finish_tile_sums(a.sum, g, s.chunk, acc_w, s2);
+  } else if (threadIdx.x == 0) {
+    add_tile_sums(a.sum, g, s.chunk, acc_w, s2);
+  }
 }
 
 // One workgroup per tile (grid-stride when the grid is capped).
-template <int K>
+template <int K, bool kOwnSums>
 __global__ __launch_bounds__(kThreads) void stage_kernel(StageArgs args) {
   (void)args;  // read below through the kernarg segment (same bytes)
   const StageArgs& a = *(const StageArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   __shared__ uint64_t red[2][kThreads / 64];
-  for (uint32_t b = blockIdx.x; b < a.ntiles; b += gridDim.x)
-    stage_tile<K>(a, a.tile0 + (a.grouped ? xcd_group<kTileGroup>(b, a.ntiles) : xcd_tile(b, a.ntiles)), red);
+  // the grid holds at most ntiles workgroups: the first tile needs no check, so its arguments load at once
+  uint32_t b = blockIdx.x;
+  do {
+    const uint32_t t = a.grouped ? xcd_group<kTileGroup>(b, a.ntiles) : xcd_tile(b, a.ntiles);
+    stage_tile<K, kOwnSums>(a, a.tile0 + t, red);
+    b += a.grid;
+  } while (b < a.ntiles);
 }
 
 // The path through host memory: packs tiles [tile0, tile0 + ntiles) into pinned host memory (dst)
@@ -274,7 +286,7 @@ __global__ __launch_bounds__(kThreads) void stage_relay_kernel(StageRelayArgs ar
 #pragma unroll
       for (int k = 0; k < R; ++k) v[k] = load_stream(a.from + min(u0 + k * kThreads, a.groups - 1));
     }
-    if (b < a.s.ntiles) stage_tile<K>(a.s, a.s.tile0 + b, red);
+    if (b < a.s.ntiles) stage_tile<K, false>(a.s, a.s.tile0 + b, red);
     if (b < reloads) {
 #pragma unroll
       for (int k = 0; k < R; ++k)
@@ -375,13 +387,15 @@ StageArgs stage_args(const StageLaunch& l) {
 
 hipError_t launch_stage_kernel(const StageLaunch& l, hipStream_t st) {
   if (!l.ntiles) return hipSuccess;
-  const StageArgs args = stage_args(l);
+  StageArgs args = stage_args(l);
   const uint32_t cap = DR_GRID_CAP > 0 ? (uint32_t)DR_GRID_CAP : kMaxGrid;
   const uint32_t grid = l.ntiles < cap ? l.ntiles : cap;
-  if (l.depth == kVecItersLarge)
-    hipLaunchKernelGGL(stage_kernel<kVecItersLarge>, dim3(grid), dim3(kThreads), 0, st, args);
-  else
-    hipLaunchKernelGGL(stage_kernel<kVecItersSmall>, dim3(grid), dim3(kThreads), 0, st, args);
+  args.grid = grid;
+  const bool own = l.sum.chunk_tiles != nullptr;
+  void (*kernel)(StageArgs) = l.depth == kVecItersLarge
+                                  ? (own ? stage_kernel<kVecItersLarge, true> : stage_kernel<kVecItersLarge, false>)
+                                  : (own ? stage_kernel<kVecItersSmall, true> : stage_kernel<kVecItersSmall, false>);
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, st, args);
   return hipGetLastError();
 }
 

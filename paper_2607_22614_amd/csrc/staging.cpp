@@ -71,6 +71,16 @@ void note_pack(const dr_plan* p, uint64_t bytes) {
   drain.store(pack_drain_ns(host_ns(), drain.load(std::memory_order_relaxed), bytes), std::memory_order_relaxed);
 }
 
+// Whether a launch of ntiles tiles sums its chunks itself: the rule at kOwnSumTiles; the ticket has
+// its word only where slots lie a line apart.
+bool own_sums(const Tiling& tl, uint32_t ntiles, hipStream_t st) {
+  static_assert(kOwnSumChunkTiles <= 64 * kTilesPerSumLine, "at most 64 slots: one wave collects them");
+  if (ntiles > kOwnSumTiles || tl.max_chunk_tiles > kOwnSumChunkTiles || tl.sum_stride != kSlotLineWords) return false;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();
+  return capture == hipStreamCaptureStatusNone;
+}
+
 // Tiles [tile0, tile0 + ntiles) of tiling tl, which cover chunks [chunk0, chunk0 + nchunks), then
 // their checksums from the accumulators of cs.
 int launch(dr_plan* p, const Tiling& tl, uint32_t tile0, uint32_t ntiles, const float* const* shards, void* dst,
@@ -82,9 +92,11 @@ int launch(dr_plan* p, const Tiling& tl, uint32_t tile0, uint32_t ntiles, const 
   l.tile0 = tile0;
   l.ntiles = ntiles;
   l.grouped = grouped;
+  if (own_sums(tl, ntiles, st)) l.sum.chunk_tiles = tl.d_chunk_tile_begin;
   hipError_t e = launch_stage_kernel(l, st);
   if (e != hipSuccess) return fail(DR_EHIP, "%s: stage kernel launch: %s", what, hipGetErrorString(e));
   p->last_depth.store(tl.depth, std::memory_order_relaxed);
+  if (l.sum.chunk_tiles) return DR_OK;
   e = launch_chunk_sums(l.sum, chunk0, nchunks, st);
   if (e != hipSuccess) return fail(DR_EHIP, "%s: chunk sum launch: %s", what, hipGetErrorString(e));
   return DR_OK;
