@@ -156,6 +156,17 @@ def _addr(x) -> int:
     raise TypeError(f"cannot take the address of {type(x)!r}")
 
 
+def _fits(x, nbytes: int) -> bool:
+    """Whether x is a dense device tensor of at least nbytes (the common case, in three attribute reads);
+    anything else is left to _buf's checks."""
+    if type(x) is int:
+        return False
+    try:
+        return x.is_cuda and x.is_contiguous() and x.nbytes >= nbytes
+    except AttributeError:
+        return False
+
+
 def _buf(x, nbytes: int, where: str, device: bool) -> int:
     """Address of a buffer the library will access as `nbytes` dense bytes.
 
@@ -165,6 +176,8 @@ def _buf(x, nbytes: int, where: str, device: bool) -> int:
     """
     if x is None or isinstance(x, int):
         return _addr(x)
+    if device and _fits(x, nbytes):
+        return x.data_ptr()
     if hasattr(x, "data_ptr"):  # torch tensor
         if not x.is_contiguous():
             raise ValueError(f"{where}: tensor is not contiguous")
@@ -195,13 +208,16 @@ def _shards(xs: Sequence, count: int, nbytes: int, where: str) -> ctypes.Array:
         return _ptr_array(xs)
     if len(xs) != count:
         raise ValueError(f"{where}: {len(xs)} shard buffers given, the plan has {count}")
-    return (ctypes.c_void_p * count)(*[_buf(x, nbytes, f"{where}[{i}]", True) for i, x in enumerate(xs)])
+    # the text that names a shard is made only for one that needs the full checks
+    return (ctypes.c_void_p * count)(*[x.data_ptr() if _fits(x, nbytes) else _buf(x, nbytes, f"{where}[{i}]", True)
+                                       for i, x in enumerate(xs)])
 
 
 def _stream(stream) -> int:
     if stream is None:
         import torch
-        return torch.cuda.current_stream().cuda_stream
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # without a Stream object around it
+        return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -318,7 +334,7 @@ def dr_stage_chunk(plan: Plan, chunk: int, shards: Sequence, dst_chunk, d_ck, st
     """shards: W device tensors/addresses; dst_chunk: device buffer; d_ck: device dr_checksum slot."""
     i = plan.info
     arr = _shards(shards, i["train_shards"] if _rollout(plan) else None, 4 * i["shard_elems"], "dr_stage_chunk shards")
-    _check(_lib.dr_stage_chunk(plan.handle, int(chunk), ctypes.cast(arr, _PP),
+    _check(_lib.dr_stage_chunk(plan.handle, int(chunk), arr,
                                _buf(dst_chunk, _chunk_len(i, int(chunk)), "dr_stage_chunk dst_chunk", True),
                                _buf(d_ck, 16, "dr_stage_chunk d_ck", True), _stream(stream)), "dr_stage_chunk")
 
@@ -329,7 +345,7 @@ def dr_stage_chunk_noalloc(plan: Plan, chunk: int, shards: Sequence, dst_chunk, 
     i = plan.info
     arr = _shards(shards, i["train_shards"] if _rollout(plan) else None, 4 * i["shard_elems"],
                   "dr_stage_chunk_noalloc shards")
-    _check(_lib.dr_stage_chunk_noalloc(plan.handle, int(chunk), ctypes.cast(arr, _PP),
+    _check(_lib.dr_stage_chunk_noalloc(plan.handle, int(chunk), arr,
                                        _buf(dst_chunk, _chunk_len(i, int(chunk)), "dr_stage_chunk_noalloc dst_chunk",
                                             True),
                                        _buf(d_ck, 16, "dr_stage_chunk_noalloc d_ck", True), _stream(stream)),
@@ -339,7 +355,7 @@ def dr_stage_chunk_noalloc(plan: Plan, chunk: int, shards: Sequence, dst_chunk, 
 def dr_stage_all(plan: Plan, shards: Sequence, dst, d_cks, stream=None) -> None:
     i = plan.info
     arr = _shards(shards, i["train_shards"] if _rollout(plan) else None, 4 * i["shard_elems"], "dr_stage_all shards")
-    _check(_lib.dr_stage_all(plan.handle, ctypes.cast(arr, _PP), _buf(dst, i["rollout_bytes"], "dr_stage_all dst", True),
+    _check(_lib.dr_stage_all(plan.handle, arr, _buf(dst, i["rollout_bytes"], "dr_stage_all dst", True),
                              _buf(d_cks, 16 * i["num_chunks"], "dr_stage_all d_cks", True), _stream(stream)),
            "dr_stage_all")
 
@@ -347,7 +363,7 @@ def dr_stage_all(plan: Plan, shards: Sequence, dst, d_cks, stream=None) -> None:
 def dr_stage_through_host(plan: Plan, shards: Sequence, dst, d_cks, stream=None) -> None:
     i = plan.info
     arr = _shards(shards, i["train_shards"] if _rollout(plan) else None, 4 * i["shard_elems"], "dr_stage_through_host shards")
-    _check(_lib.dr_stage_through_host(plan.handle, ctypes.cast(arr, _PP),
+    _check(_lib.dr_stage_through_host(plan.handle, arr,
                                       _buf(dst, i["rollout_bytes"], "dr_stage_through_host dst", True),
                                       _buf(d_cks, 16 * i["num_chunks"], "dr_stage_through_host d_cks", True),
                                       _stream(stream)), "dr_stage_through_host")
@@ -358,7 +374,7 @@ def dr_reshard(plan: Plan, src_shards: Sequence, dst_shards: Sequence, d_cks, st
     ok = i["kind"] == DR_PLAN_RESHARD
     a = _shards(src_shards, i["train_shards"] if ok else None, 4 * i["shard_elems"], "dr_reshard src_shards")
     b = _shards(dst_shards, i["dst_shards"] if ok else None, 4 * i["dst_shard_elems"], "dr_reshard dst_shards")
-    _check(_lib.dr_reshard(plan.handle, ctypes.cast(a, _PP), ctypes.cast(b, _PP),
+    _check(_lib.dr_reshard(plan.handle, a, b,
                            _buf(d_cks, 16 * i["num_chunks"], "dr_reshard d_cks", True), _stream(stream)), "dr_reshard")
 
 
@@ -368,7 +384,7 @@ def dr_reshard_through_host(plan: Plan, src_shards: Sequence, dst_shards: Sequen
     a = _shards(src_shards, i["train_shards"] if ok else None, 4 * i["shard_elems"], "dr_reshard_through_host src_shards")
     b = _shards(dst_shards, i["dst_shards"] if ok else None, 4 * i["dst_shard_elems"],
                 "dr_reshard_through_host dst_shards")
-    _check(_lib.dr_reshard_through_host(plan.handle, ctypes.cast(a, _PP), ctypes.cast(b, _PP),
+    _check(_lib.dr_reshard_through_host(plan.handle, a, b,
                                         _buf(d_cks, 16 * i["num_chunks"], "dr_reshard_through_host d_cks", True),
                                         _stream(stream)), "dr_reshard_through_host")
 
@@ -382,20 +398,20 @@ def _moment_args(plan: Plan, m_shards: Sequence, v_shards: Sequence, host_store,
 
 def dr_offload_moments(plan: Plan, m_shards: Sequence, v_shards: Sequence, host_store, side_stream) -> None:
     m, v, store = _moment_args(plan, m_shards, v_shards, host_store, "dr_offload_moments")
-    _check(_lib.dr_offload_moments(plan.handle, ctypes.cast(m, _PP), ctypes.cast(v, _PP), store,
+    _check(_lib.dr_offload_moments(plan.handle, m, v, store,
                                    _stream(side_stream)), "dr_offload_moments")
 
 
 def dr_restore_moments(plan: Plan, host_store, m_shards: Sequence, v_shards: Sequence, side_stream) -> None:
     m, v, store = _moment_args(plan, m_shards, v_shards, host_store, "dr_restore_moments")
-    _check(_lib.dr_restore_moments(plan.handle, store, ctypes.cast(m, _PP), ctypes.cast(v, _PP),
+    _check(_lib.dr_restore_moments(plan.handle, store, m, v,
                                    _stream(side_stream)), "dr_restore_moments")
 
 
 def dr_offload_moments_range(plan: Plan, m_shards: Sequence, v_shards: Sequence, host_store, first_chunk: int,
                              num_chunks: int, side_stream) -> None:
     m, v, store = _moment_args(plan, m_shards, v_shards, host_store, "dr_offload_moments_range")
-    _check(_lib.dr_offload_moments_range(plan.handle, ctypes.cast(m, _PP), ctypes.cast(v, _PP), store,
+    _check(_lib.dr_offload_moments_range(plan.handle, m, v, store,
                                          int(first_chunk), int(num_chunks), _stream(side_stream)),
            "dr_offload_moments_range")
 
@@ -403,7 +419,7 @@ def dr_offload_moments_range(plan: Plan, m_shards: Sequence, v_shards: Sequence,
 def dr_restore_moments_range(plan: Plan, host_store, m_shards: Sequence, v_shards: Sequence, first_chunk: int,
                              num_chunks: int, side_stream) -> None:
     m, v, store = _moment_args(plan, m_shards, v_shards, host_store, "dr_restore_moments_range")
-    _check(_lib.dr_restore_moments_range(plan.handle, store, ctypes.cast(m, _PP), ctypes.cast(v, _PP),
+    _check(_lib.dr_restore_moments_range(plan.handle, store, m, v,
                                          int(first_chunk), int(num_chunks), _stream(side_stream)),
            "dr_restore_moments_range")
 
@@ -414,7 +430,7 @@ def dr_restore_moments_begin(plan: Plan, host_store, m_shards: Sequence, v_shard
     none of them is freed while the thread still copies."""
     m, v, store = _moment_args(plan, m_shards, v_shards, host_store, "dr_restore_moments_begin")
     refs = (host_store, tuple(m_shards), tuple(v_shards), side_stream)
-    _check(_lib.dr_restore_moments_begin(plan.handle, store, ctypes.cast(m, _PP), ctypes.cast(v, _PP),
+    _check(_lib.dr_restore_moments_begin(plan.handle, store, m, v,
                                          _stream(side_stream)), "dr_restore_moments_begin")
     plan._restore_refs = refs
 
@@ -431,7 +447,7 @@ def dr_moment_checksums(plan: Plan, m_shards: Sequence, v_shards: Sequence, d_ck
     i = plan.info
     m = _shards(m_shards, i["train_shards"], 4 * i["shard_elems"], "dr_moment_checksums m_shards")
     v = _shards(v_shards, i["train_shards"], 4 * i["shard_elems"], "dr_moment_checksums v_shards")
-    _check(_lib.dr_moment_checksums(plan.handle, ctypes.cast(m, _PP), ctypes.cast(v, _PP),
+    _check(_lib.dr_moment_checksums(plan.handle, m, v,
                                     _buf(d_cks, 16 * i["num_moment_chunks"], "dr_moment_checksums d_cks", True),
                                     _stream(stream)), "dr_moment_checksums")
 
