@@ -16,7 +16,11 @@
 namespace dr {
 namespace {
 
-constexpr uint32_t kPartGroup = 64;
+// A workgroup's part of a tile (groups per lane), and the parts of a group in grouped order.
+constexpr int kPartIters = 2;
+constexpr uint32_t kPartGroup = 32;
+constexpr uint32_t kTileParts = kReshardIters / kPartIters;
+static_assert(kTileParts == 2, "a tile is two parts");
 
 struct ReshardArgs {
   const DevSeg* segs;
@@ -76,14 +80,15 @@ __device__ __forceinline__ void reshard_tile(const ReshardArgs& a, uint32_t g, u
   if (threadIdx.x == 0) add_tile_sums(a.sum, g, s.chunk, acc_w, (pos0 + 1) * acc_w + acc_rw);
 }
 
-// A workgroup moves one part of a tile, one 16-byte group per lane, and the XCDs take groups of 64
-// parts (256 KiB) in turn.  Bound by HBM, where the read and the write stream meet in the same
-// banks: how they fall together depends on the tile's size, on the order and on where the
-// buffers lie.  The 8B shape at 16 layers, 8 to 6 shards (36.3 GB): whole tiles per workgroup,
-// each XCD on its own eighth of the stream 5.65-5.92 ms by process; halves in that order
-// 5.69-6.03, quarters 5.63, quarters in groups of 16 / 64 / 256: 5.90 / 5.56 / 5.62.  At 32 layers
-// 9.64-10.51 against 9.86-9.97 (64); 0.5B 0.830 against 0.777; 5 to 3 shards of an odd width
-// 0.939 against 0.842.
+// A workgroup moves half a tile, two 16-byte groups per lane, and the XCDs take groups of 32 halves
+// (256 KiB) in turn.  Bound by HBM, where the read and the write stream meet in the same banks:
+// how they fall together depends on the tile's size, on the order and on where the buffers lie.
+// The 8B shape at 16 layers, 8 to 6 shards (36.3 GB), back to back / after 50 ms idle, when the clock
+// is lower: whole tiles per workgroup, each XCD on its own eighth of the stream 5.87 / 5.93 ms;
+// halves in that order 5.69-6.03 / 6.10; halves in groups of 16 / 32 / 64 / 256: 5.86 / 5.63 / 5.84
+// / 5.80 (32: 5.75 after idle); quarters in groups of 64 5.59 / 6.16.  At 32 layers 9.83-10.51 /
+// 10.44 before, 9.99-10.18 / 10.11 now; 0.5B 0.830 / 0.881 and 0.797 / 0.857; 5 to 3 shards of an odd
+// width 0.940 / 1.00 and 0.865 / 0.937.
 __global__ __launch_bounds__(kThreads) void reshard_kernel(ReshardArgs args) {
   (void)args;  // read through the kernarg segment (same bytes)
   const ReshardArgs& a = *(const ReshardArgs*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -92,7 +97,7 @@ __global__ __launch_bounds__(kThreads) void reshard_kernel(ReshardArgs args) {
   for (uint64_t b = blockIdx.x; b < n; b += gridDim.x) {
     const uint64_t t = xcd_group<kPartGroup>(b, n);
     const uint32_t part = (uint32_t)t & ((1u << a.part_shift) - 1);
-    reshard_tile<1>(a, a.tile0 + (uint32_t)(t >> a.part_shift), part * kThreads, red);
+    reshard_tile<kPartIters>(a, a.tile0 + (uint32_t)(t >> a.part_shift), part * kPartIters * kThreads, red);
   }
 }
 
@@ -100,10 +105,6 @@ __global__ __launch_bounds__(kThreads) void reshard_kernel(ReshardArgs args) {
 // and reloads what the previous launch packed into the destination shards, in alternation
 // (the reason is at the stage kernel's form).  A step is half a tile, 8 KiB each way.  2.7 GB each
 // way in 8 MiB chunks, 5 to 3 shards: 77.5 -> 60.4 ms (a packing kernel and copies before).
-constexpr int kRelayIters = 2;
-constexpr uint32_t kTileSteps = kReshardIters / kRelayIters;
-static_assert(kReshardIters % kRelayIters == 0, "whole steps per tile");
-
 struct ReshardRelayArgs {
   ReshardArgs s;
   const u32x4* from;  // pinned, 16-byte groups of the previous launch
@@ -116,20 +117,20 @@ __global__ __launch_bounds__(kThreads) void reshard_relay_kernel(ReshardRelayArg
   (void)args;  // read through the kernarg segment (same bytes)
   const ReshardRelayArgs& a = *(const ReshardRelayArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   __shared__ uint64_t red[2][kThreads / 64];
-  constexpr uint32_t per = kThreads * kRelayIters;
-  const uint32_t reloads = (a.groups + per - 1) / per, packs = a.s.ntiles * kTileSteps, steps = max(packs, reloads);
+  constexpr uint32_t per = kThreads * kPartIters;
+  const uint32_t reloads = (a.groups + per - 1) / per, packs = a.s.ntiles * kTileParts, steps = max(packs, reloads);
   const uint64_t S2 = a.s.dst_shard_elems;
   for (uint32_t b = blockIdx.x; b < steps; b += gridDim.x) {
     const uint32_t u0 = b * per + threadIdx.x;
-    u32x4 v[kRelayIters];
+    u32x4 v[kPartIters];
     if (b < reloads) {
 #pragma unroll
-      for (int k = 0; k < kRelayIters; ++k) v[k] = load_stream(a.from + min(u0 + k * kThreads, a.groups - 1));
+      for (int k = 0; k < kPartIters; ++k) v[k] = load_stream(a.from + min(u0 + k * kThreads, a.groups - 1));
     }
-    if (b < packs) reshard_tile<kRelayIters>(a.s, a.s.tile0 + b / kTileSteps, b % kTileSteps * per, red);
+    if (b < packs) reshard_tile<kPartIters>(a.s, a.s.tile0 + b / kTileParts, b % kTileParts * per, red);
     if (b < reloads) {
 #pragma unroll
-      for (int k = 0; k < kRelayIters; ++k) {
+      for (int k = 0; k < kPartIters; ++k) {
         const uint32_t u = u0 + k * kThreads;
         if (u < a.groups) {
           const uint64_t e = a.elem0 + 4ull * u;
@@ -169,11 +170,8 @@ ReshardArgs reshard_args(const ReshardLaunch& l) {
 hipError_t launch_reshard_kernel(const ReshardLaunch& l, hipStream_t st) {
   if (!l.ntiles) return hipSuccess;
   ReshardArgs args = reshard_args(l);
-  // as many parts of kThreads groups as the largest tile has: fewer than kReshardIters where a
-  // chunk is smaller than a tile
-  static_assert(kReshardIters == 4, "tiles of up to 4 parts");
-  const uint64_t groups = l.chunk_elems / 4;
-  args.part_shift = groups <= (uint64_t)kThreads ? 0 : groups <= 2ull * kThreads ? 1 : 2;
+  // one part where a chunk, and so a tile, holds no more groups than a part
+  args.part_shift = l.chunk_elems / 4 <= (uint64_t)kPartIters * kThreads ? 0 : 1;
   const uint64_t grid = std::min<uint64_t>((uint64_t)l.ntiles << args.part_shift, kMaxGrid);
   hipLaunchKernelGGL(reshard_kernel, dim3((uint32_t)grid), dim3(kThreads), 0, st, args);
   return hipGetLastError();
@@ -187,9 +185,9 @@ hipError_t launch_reshard_relay(const ReshardLaunch& l, const Reload& r, hipStre
   args.elem0 = r.elem0;
   args.groups = r.groups;
   args.shard0 = (uint32_t)(r.elem0 / l.dst_shard_elems);
-  constexpr uint32_t per = kThreads * kRelayIters;
+  constexpr uint32_t per = kThreads * kPartIters;
   static_assert(16 * per == kRelayTileBytes, "a step moves kRelayTileBytes each way");
-  const uint32_t steps = std::max(l.ntiles * kTileSteps, (r.groups + per - 1) / per);
+  const uint32_t steps = std::max(l.ntiles * kTileParts, (r.groups + per - 1) / per);
   hipLaunchKernelGGL(reshard_relay_kernel, dim3(std::min(steps, kReshardRelayGrid)), dim3(kThreads), 0, st, args);
   return hipGetLastError();
 }
