@@ -12,7 +12,7 @@ def _xcd_group(b, n, G):
     return (i // G * XCDS + x) * G + i % G
 
 
-@pytest.mark.parametrize("G", [32, 64])  # kPartGroup (reshard.hip), kTileGroup (stage.hip)
+@pytest.mark.parametrize("G", [32, 64])  # kPartGroup (reshard.hip), kTileGroup (stage.hip, moment_sums.hip)
 @pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 511, 512, 513, 1023, 1024, 1025, 1536, 4099, 8192, 10000])
 def test_grouped_order_is_a_permutation(n, G):
     t = np.array([_xcd_group(b, n, G) for b in range(n)])
