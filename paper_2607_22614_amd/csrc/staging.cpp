@@ -33,12 +33,15 @@ int check_device(const dr_plan* p, const char* what) {
 // Tile order of a launch.  A short launch is mostly its start, when nothing of source, destination
 // and tables has been touched for a while: in grouped order the chip works on one window of 512
 // tiles, in contiguous order on eight places of the stream at once.  Once the launch runs, contiguous
-// order is the faster one.  One-chunk launches (measured on loops of them) take grouped order: 64
-// MiB chunks of 0.5B 732 -> 686 us for 20 calls, 256 MiB chunks of 8B 7.82 -> 7.71 ms for 60
-// (groups of 4-32 and 128-256 tiles: 686-732 us, 7.82-8.09 ms).  So does a lone pack (deep
-// tiling) up to kGroupedLoneBytes: 0.5 / 1.8 / 3.8 GB moved after 30 ms idle 218 / 379 / 638 us contiguous,
-// 203 / 355 / 635 grouped, but 16 / 48 GB 2.73 / 7.55 ms against 2.78 / 7.66.  Packs behind packs stay
-// contiguous: 0.27 / 0.57 / 7.31 ms against 0.28 / 0.58 / 7.46.
+// order is the faster one.  Measured contiguous / grouped by 64 tiles:
+//   one chunk a launch (loops of them): 20 of 64 MiB (0.5B) 732 / 687 us, 60 of 256 MiB (8B) 7.82 / 7.73
+//   ms (groups of 4-32 and 128-256 tiles: 686-732 us, 7.82-8.09 ms): grouped;
+//   whole streams behind another pack, by GB moved: 0.2 34.3 / 33.1 us, 0.4 62.2 / 59.8, 0.5 88.9 /
+//   85.1, 0.7 115.5 / 110.8, 1.1 172.6 / 171.3, 1.4 213 / 217, 3.8 571 / 580, 48 7312 / 7457: grouped up
+//   to kGroupedBytes;
+//   whole streams after 30 ms idle (the deep tiling): 0.5 218 / 203 us, 1.8 379 / 355, 3.8 638 / 635, 16
+//   2730 / 2780, 48 7550 / 7660: grouped up to kGroupedLoneBytes.
+constexpr uint64_t kGroupedBytes = 1ull << 30;
 constexpr uint64_t kGroupedLoneBytes = 4ull << 30;
 
 // Per-device state of the automatic tile depth (see pack_drain_ns in the
@@ -263,7 +266,7 @@ extern "C" int dr_stage_all(dr_plan* p, const float* const* shards, void* dst, d
   const Tiling& tl = p->tiling[pick];
   const uint64_t bytes = 4 * p->info.n_elems + p->info.rollout_bytes;
   const int rc = launch(p, tl, 0, (uint32_t)tl.tiles.size(), shards, dst, 0, 0, (uint32_t)p->info.num_chunks,
-                        pick == 1 && bytes <= kGroupedLoneBytes, chunk_sum(p, tl, d_cks, 0),
+                        bytes <= (pick == 1 ? kGroupedLoneBytes : kGroupedBytes), chunk_sum(p, tl, d_cks, 0),
                         static_cast<hipStream_t>(stream), "dr_stage_all");
   if (rc == DR_OK) note_pack(p, bytes);
   return rc;
