@@ -273,9 +273,10 @@ int dr_stage_chunk(dr_plan* plan, uint64_t chunk, const float* const* shards, vo
  * the same kernels, but the chunk's checksum accumulators live in a fixed
  * static device array of the library (32 KiB per GPU, kept until the process
  * ends) instead of the plan's.  The call allocates nothing (no hipMalloc, no
- * allocating library call); it launches the stage and chunk-sum kernels.  The
- * first call on a GPU clears the array with a small kernel first, and every
- * call leaves it at zero (the chunk-sum kernel clears the slots it reads);
+ * allocating library call); it launches the stage kernel and, but for small
+ * chunks outside a graph, the chunk-sum kernel.  The first call on a GPU clears
+ * the array with a small kernel first, and every call leaves it at zero (what
+ * sums the slots clears them);
  * after a call that failed, the following calls clear it first again, up to
  * and including the first one that is not recorded into a graph.
  * Every call on a GPU shares that GPU's array: calls that overlap on one GPU

@@ -5,7 +5,8 @@
 // instead of the plan's accumulators; the kernels are the same.
 //
 // The first call on a GPU clears the array with a small kernel, and every call
-// leaves it at zero again: the chunk-sum kernel clears each slot it reads.  A
+// leaves it at zero again: whoever sums the slots (the chunk-sum kernel, or the
+// last tile of a small launch) clears them.  A
 // call that fails after its stage kernel may have run marks the GPU's array
 // again.  While the array is marked, calls clear it before staging, until one
 // that is not being recorded into a graph has done so.

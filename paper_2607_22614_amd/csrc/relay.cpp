@@ -107,8 +107,9 @@ uint64_t packed_before(const dr_plan* p, const Tiling& tl, uint32_t t, uint64_t 
   return (e * elem_bytes - chunk * p->layout.chunk_bytes) & ~15ull;
 }
 
-// Store and reload by kernels, all on st.  launch(piece, pin, prev, from) enqueues the launch that packs
-// *piece (null: nothing) into pin and reloads *prev (null: nothing) from `from`.
+// Store and reload by kernels.  launch(piece, prev) enqueues the launch that packs *piece (null:
+// nothing) into its chunk's pinned buffer and reloads *prev (null: nothing) from its own.  A buffer
+// is packed again two chunks later, at least one launch after its last piece was reloaded.
 template <typename Launch>
 int relay_kernels(dr_plan* p, const Tiling& tl, uint32_t elem_bytes, uint32_t tile_bytes, Launch launch) {
   const uint32_t most = std::max<uint32_t>(1, kRelayPieceBytes / tile_bytes);
@@ -179,7 +180,7 @@ int relay_finish(dr_plan* p, hipStream_t st, const char* what) {
   return e == hipSuccess ? DR_OK : relay_hip(e, what, "record end of call");
 }
 
-// The relay pipeline shared by the rollout and reshard plans.  pack(c, buf) enqueues on st the
+// Store by kernels, reload by copies, shared by the rollout and reshard plans.  pack(c, buf) enqueues on st the
 // kernels that write chunk c into pinned buffer buf; reload(c, buf, in) enqueues on the plan's
 // copy stream the host->device copies that move it to its destination.
 template <typename Pack, typename Reload>
