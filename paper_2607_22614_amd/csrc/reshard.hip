@@ -186,7 +186,6 @@ hipError_t launch_reshard_relay(const ReshardLaunch& l, const Reload& r, hipStre
   args.groups = r.groups;
   args.shard0 = (uint32_t)(r.elem0 / l.dst_shard_elems);
   constexpr uint32_t per = kThreads * kPartIters;
-  static_assert(16 * per == kRelayTileBytes, "a step moves kRelayTileBytes each way");
   const uint32_t steps = std::max(l.ntiles * kTileParts, (r.groups + per - 1) / per);
   hipLaunchKernelGGL(reshard_relay_kernel, dim3(std::min(steps, kReshardRelayGrid)), dim3(kThreads), 0, st, args);
   return hipGetLastError();

@@ -407,7 +407,7 @@ hipError_t launch_stage_relay(const StageLaunch& l, const Reload& r, hipStream_t
   args.to = static_cast<u32x4*>(r.to);
   args.groups = r.groups;
   const uint32_t per = kThreads * (l.depth / 2), steps = std::max(l.ntiles, (r.groups + per - 1) / per);
-  const uint32_t grid = std::min(steps, kRelayTileBytes / (16 * per) * kStageRelayGrid);
+  const uint32_t grid = std::min(steps, std::max(1u, kRelayTileBytes / (16 * per)) * kStageRelayGrid);
   if (l.depth == kVecItersLarge)
     hipLaunchKernelGGL(stage_relay_kernel<kVecItersLarge>, dim3(grid), dim3(kThreads), 0, st, args);
   else
