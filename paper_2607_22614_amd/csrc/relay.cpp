@@ -197,11 +197,8 @@ int relay_copies(dr_plan* p, hipStream_t st, const char* what, Pack pack, Reload
   hipEvent_t* copied_in = ev + 2;  // relay_pin[b] reloaded: relay_pin[b] free
   hipEvent_t start = ev[4];        // the caller's earlier work on `st` (e.g. readers of the destination)
   hipError_t e;
-#define DR_RELAY(call, step)             \
-  if ((e = (call)) != hipSuccess) {      \
-    (void)hipStreamSynchronize(in);      \
-    return relay_hip(e, what, step);     \
-  }
+#define DR_RELAY(call, step) \
+  if ((e = (call)) != hipSuccess) return relay_hip(e, what, step)
   DR_RELAY(hipEventRecord(start, st), "record start");
   DR_RELAY(hipStreamWaitEvent(in, start, 0), "wait start");
   for (uint64_t c = 0; c < p->info.num_chunks; ++c) {
@@ -227,13 +224,17 @@ int relay_call(dr_plan* p, hipStream_t st, const char* what, Run run) {
   RelayHeld held;
   if (int rc = held.take(p, what)) return rc;
   if (int rc = relay_begin(p, st, what)) return rc;
-  if (int rc = run()) {
-    // what was enqueued still uses the pinned buffers: the next call is ordered after it
-    if (p->relay_ev[4]) (void)hipEventRecord(static_cast<hipEvent_t>(p->relay_ev[4]), st);
+  int rc = run();
+  if (rc == DR_OK) rc = relay_finish(p, st, what);
+  if (rc) {
+    // What was enqueued still uses the pinned buffers.  No copy is left running (a later call that
+    // reloads by kernels waits for none), and the next call is ordered after the kernels.
+    if (p->relay_stream) (void)hipStreamSynchronize(static_cast<hipStream_t>(p->relay_stream));
+    hipEvent_t end = static_cast<hipEvent_t>(p->relay_ev[4]);
+    if (end && hipEventRecord(end, st) != hipSuccess) (void)hipStreamSynchronize(st);
     (void)hipGetLastError();
-    return rc;
   }
-  return relay_finish(p, st, what);
+  return rc;
 }
 
 }  // namespace

@@ -1,0 +1,295 @@
+// The library's host code (plans, launches, the paths through host memory) on the CPU, over the
+// stand-in runtime of fake_hip.h and plain loops in place of the kernels: what is enqueued, in what
+// order, and what is left behind when a call fails or a plan goes away.
+//   host_check copies|sums|destroy
+// Exit status 0 when everything holds.
+#include "fake_hip.h"
+
+#include <algorithm>
+#include <cstdint>
+#include <string>
+
+#include "dr_internal.h"
+#include "kernels.h"
+
+static int errors = 0;
+#define CHECK(c, ...)                                   \
+  do {                                                  \
+    if (!(c)) {                                         \
+      if (errors < 20) {                                \
+        std::fprintf(stderr, "FAIL %s: ", #c);          \
+        std::fprintf(stderr, __VA_ARGS__);              \
+        std::fprintf(stderr, "\n");                     \
+      }                                                 \
+      ++errors;                                         \
+    }                                                   \
+  } while (0)
+
+namespace dr {
+
+// The kernels as loops.  They read their tables when they run, like the kernels.
+namespace {
+
+struct StageRecord {  // every stage launch, in order
+  uint32_t ntiles, groups;
+  bool relay, grouped;
+  int depth;
+};
+std::vector<StageRecord> launched;
+
+uint16_t bf16(float x) {  // finite inputs
+  uint32_t u;
+  std::memcpy(&u, &x, 4);
+  return (uint16_t)((u + 0x7FFF + ((u >> 16) & 1)) >> 16);
+}
+
+void add_sums(const ChunkSum& cs, uint32_t tile, uint32_t chunk, uint64_t s1, uint64_t s2) {
+  fake::touch(cs.acc);
+  uint64_t* slots = cs.acc + (uint64_t)(chunk - cs.chunk_bias) * cs.sub * cs.stride_words;
+  slots[(tile & (cs.sub - 1)) * cs.stride_words] += s1;
+  slots[(tile & (cs.sub - 1)) * cs.stride_words + 1] += s2;
+}
+
+void finish_chunk(const ChunkSum& cs, uint32_t chunk) {
+  uint64_t* slots = cs.acc + (uint64_t)(chunk - cs.chunk_bias) * cs.sub * cs.stride_words;
+  dr_checksum& out = cs.out[chunk - cs.out_chunk0];
+  out.s1 = out.s2 = 0;
+  for (uint32_t i = 0; i < cs.sub; ++i) {
+    out.s1 += slots[i * cs.stride_words];
+    out.s2 += slots[i * cs.stride_words + 1];
+    slots[i * cs.stride_words] = slots[i * cs.stride_words + 1] = 0;
+  }
+}
+
+// The elements of an unaligned tile lie on the destination's grid of 4: `lead` elements back from
+// its first unit; the segment's last tile goes to the segment's end.
+void stage_tiles(const StageLaunch& l, const std::vector<const float*>& shards) {
+  for (uint32_t g = l.tile0; g < l.tile0 + l.ntiles; ++g) {
+    const Tile t = l.tiles[g];
+    const DevSeg& s = l.segs[t.seg];
+    const uint64_t pos0 = s.dst - s.chunk * l.chunk_elems;
+    uint64_t e0, e1;
+    if (s.flags & DR_SEG_VEC4) {
+      e0 = 4ull * t.unit0;
+      e1 = 4ull * std::min(s.units, t.unit0 + kThreads * (uint32_t)l.depth);
+    } else {
+      const uint32_t lead = pos0 & 3;
+      e0 = t.unit0 ? t.unit0 - lead : 0;
+      e1 = t.unit0 + kScalarUnitsPerTile >= s.units ? s.units : t.unit0 + kScalarUnitsPerTile - lead;
+    }
+    uint16_t* out = static_cast<uint16_t*>(l.dst) + (s.dst - l.dst_bias);
+    fake::touch(out + e0);
+    uint64_t s1 = 0, s2 = 0;
+    for (uint64_t e = e0; e < e1; ++e) {
+      const uint16_t v = bf16(shards[s.shard][s.src + e / s.cols * s.stride + e % s.cols]);
+      out[e] = v;
+      const uint64_t pos = pos0 + e, w = (uint64_t)v << (pos & 1) * 16;
+      s1 += w;
+      s2 += ((pos >> 1) + 1) * w;
+    }
+    add_sums(l.sum, g, s.chunk, s1, s2);
+    if (l.sum.chunk_tiles) {
+      uint32_t& ticket = *reinterpret_cast<uint32_t*>(
+          l.sum.acc + (uint64_t)(s.chunk - l.sum.chunk_bias) * l.sum.sub * l.sum.stride_words + kTicketWord);
+      if (++ticket == l.sum.chunk_tiles[s.chunk + 1] - l.sum.chunk_tiles[s.chunk]) {
+        ticket = 0;
+        finish_chunk(l.sum, s.chunk);
+      }
+    }
+  }
+}
+
+void reshard_tiles(const ReshardLaunch& l, const std::vector<const float*>& src, const std::vector<float*>& dst) {
+  for (uint32_t g = l.tile0; g < l.tile0 + l.ntiles; ++g) {
+    const Tile t = l.tiles[g];
+    const DevSeg& s = l.segs[t.seg];
+    const uint64_t pos0 = s.dst - s.chunk * l.chunk_elems;
+    uint64_t s1 = 0, s2 = 0;
+    for (uint64_t e = 4ull * t.unit0; e < 4ull * std::min(s.units, t.unit0 + kThreads * kReshardIters); ++e) {
+      uint32_t w = 0;
+      if (s.op != DR_OP_ZERO_F32) std::memcpy(&w, src[s.shard] + s.src + e, 4);
+      float* out = l.flat ? l.flat + (s.dst - l.flat_bias) : dst[s.dst_shard] + (s.dst - s.dst_shard * l.dst_shard_elems);
+      if (e == 4ull * t.unit0) fake::touch(out + e);
+      std::memcpy(out + e, &w, 4);
+      s1 += w;
+      s2 += (pos0 + e + 1) * w;
+    }
+    add_sums(l.sum, g, s.chunk, s1, s2);
+  }
+}
+
+}  // namespace
+
+int scratch_on(int, uint64_t** out) { return *out = nullptr, DR_OK; }
+
+hipError_t launch_stage_kernel(const StageLaunch& l, hipStream_t st) {
+  launched.push_back({l.ntiles, 0, false, l.grouped, l.depth});
+  std::vector<const float*> shards(l.shards, l.shards + l.num_shards);
+  return fake::launch(st, [=] { stage_tiles(l, shards); });
+}
+
+hipError_t launch_stage_relay(const StageLaunch& l, const Reload& r, hipStream_t st) {
+  launched.push_back({l.ntiles, r.groups, true, l.grouped, l.depth});
+  std::vector<const float*> shards(l.shards, l.shards + l.num_shards);
+  return fake::launch(st, [=] {  // the reload first or last: the launch leaves it open
+    const bool first = l.tile0 & 1;
+    for (int k = 0; k < 2; ++k) {
+      if ((k == 0) != first && l.ntiles) stage_tiles(l, shards);
+      if ((k == 0) == first && r.groups) {
+        fake::touch(r.from);
+        fake::touch(r.to);
+        std::memcpy(r.to, r.from, 16ull * r.groups);
+      }
+    }
+  });
+}
+
+hipError_t launch_chunk_sums(const ChunkSum& cs, uint32_t chunk0, uint32_t n, hipStream_t st) {
+  return fake::launch(st, [=] {
+    fake::touch(cs.acc);
+    for (uint32_t c = chunk0; c < chunk0 + n; ++c) finish_chunk(cs, c);
+  });
+}
+
+hipError_t launch_reshard_kernel(const ReshardLaunch& l, hipStream_t st) {
+  std::vector<const float*> src(l.src, l.src + l.num_src);
+  std::vector<float*> dst;
+  if (l.dst) dst.assign(l.dst, l.dst + l.num_dst);
+  return fake::launch(st, [=] { reshard_tiles(l, src, dst); });
+}
+
+hipError_t launch_reshard_relay(const ReshardLaunch& l, const Reload& r, hipStream_t st) {
+  launched.push_back({l.ntiles, r.groups, true, false, 0});
+  std::vector<const float*> src(l.src, l.src + l.num_src);
+  std::vector<float*> dst(l.dst, l.dst + l.num_dst);
+  return fake::launch(st, [=] {
+    const bool first = l.tile0 & 1;
+    for (int k = 0; k < 2; ++k) {
+      if ((k == 0) != first && l.ntiles) reshard_tiles(l, src, dst);
+      if ((k == 0) == first && r.groups) fake::touch(r.from);
+      if ((k == 0) == first)
+        for (uint64_t i = 0; i < 4ull * r.groups; ++i) {
+          const uint64_t e = r.elem0 + i;
+          std::memcpy(dst[e / l.dst_shard_elems] + e % l.dst_shard_elems, static_cast<const float*>(r.from) + i, 4);
+        }
+    }
+  });
+}
+
+}  // namespace dr
+
+using namespace dr;
+
+namespace {
+
+// A plan with sources and expected output (from one dr_stage_all or dr_reshard, checked elsewhere
+// against the oracle's definition of the layout), and what a call on it produces.
+struct Work {
+  dr_plan* p = nullptr;
+  std::vector<float*> src;
+  std::vector<uint8_t> want;
+  std::vector<dr_checksum> want_cks;
+  uint8_t *dst = nullptr, *pinned = nullptr;
+  dr_checksum* cks = nullptr;
+  std::vector<float*> shards_of(uint8_t* at) {
+    std::vector<float*> v;
+    for (int w = 0; w < p->dst_shards; ++w) v.push_back(reinterpret_cast<float*>(at) + w * p->dst_shard_elems);
+    return v;
+  }
+  void clear() {
+    std::memset(dst, 0xEE, p->info.rollout_bytes);
+    std::memset(pinned, 0xEE, p->info.rollout_bytes);
+    std::memset(static_cast<void*>(cks), 0xEE, p->info.num_chunks * sizeof(dr_checksum));
+  }
+  bool right(const uint8_t* at) const {
+    return !std::memcmp(at, want.data(), want.size()) &&
+           !std::memcmp(cks, want_cks.data(), want_cks.size() * sizeof(dr_checksum));
+  }
+  int all(hipStream_t st) {
+    if (p->kind == kRollout) return dr_stage_all(p, src.data(), dst, cks, st);
+    return dr_reshard(p, src.data(), shards_of(dst).data(), cks, st);
+  }
+  int through_host(uint8_t* to, hipStream_t st) {
+    if (p->kind == kRollout) return dr_stage_through_host(p, src.data(), to, cks, st);
+    return dr_reshard_through_host(p, src.data(), shards_of(to).data(), cks, st);
+  }
+};
+
+Work setup(const dr_model& m, int w, int to, uint64_t chunk, int depth = 0) {
+  Work k;
+  const dr_layout l{w, to, chunk, 0, depth, 0};
+  const int rc = to < 0 ? dr_reshard_plan_create(&m, w, -to, chunk, &k.p) : dr_plan_create(&m, &l, &k.p);
+  if (rc) std::fprintf(stderr, "plan: %s\n", dr_last_error()), std::exit(2);
+  uint32_t x = 12345;
+  for (int i = 0; i < w; ++i) {
+    void* p;
+    fake::add(&p, 4 * k.p->info.shard_elems, true);
+    float* f = static_cast<float*>(p);
+    for (uint64_t e = 0; e < k.p->info.shard_elems; ++e) f[e] = (float)((x = x * 1664525 + 1013904223) >> 8) - 8e6f;
+    k.src.push_back(f);
+  }
+  void* p;
+  fake::add(&p, k.p->info.rollout_bytes, true), k.dst = static_cast<uint8_t*>(p);
+  fake::add(&p, k.p->info.rollout_bytes, false), k.pinned = static_cast<uint8_t*>(p);
+  fake::add(&p, k.p->info.num_chunks * sizeof(dr_checksum), true), k.cks = static_cast<dr_checksum*>(p);
+  k.clear();
+  if (k.all(nullptr)) std::exit(2);
+  (void)hipDeviceSynchronize();
+  k.want.assign(k.dst, k.dst + k.p->info.rollout_bytes);
+  k.want_cks.assign(k.cks, k.cks + k.p->info.num_chunks);
+  return k;
+}
+
+hipStream_t stream() {
+  hipStream_t s;
+  (void)hipStreamCreateWithFlags(&s, 0);
+  return s;
+}
+
+const dr_model kSmall{2, 64, 6, 3, 24, 3 * 37, 3 * 41};  // column slices of any alignment at T = 3
+
+// f(n) for n = 1, 2, ... until it is false; f passes n to failing_call, which has enqueue n of one call fail.
+template <typename F>
+long each_failure(F f) {
+  long n = 1;
+  while (f(n)) ++n;
+  return n - 1;
+}
+template <typename F>
+int failing_call(long n, F call) {
+  fake::enqueues = 0;
+  fake::fail_at = n;
+  const int rc = call();
+  fake::fail_at = 0;
+  return rc;
+}
+
+// A call that fails on the way leaves none of its reload copies running.
+void check_copies() {
+  for (int to : {3, -2}) {
+    const long n = each_failure([&](long i) {
+      Work k = setup(kSmall, 4, to, 4096);
+      const hipStream_t st = stream();
+      const int rc = failing_call(i, [&] { return k.through_host(k.pinned, st); });
+      const fake::Stream* in = fake::of(static_cast<hipStream_t>(k.p->relay_stream));
+      CHECK(!rc || !k.p->relay_stream || in->ops.empty(), "enqueue %ld: %zu left on the copy stream", i, in->ops.size());
+      (void)hipDeviceSynchronize();
+      if (!rc) CHECK(k.right(k.pinned), "through host");
+      dr_plan_destroy(k.p);
+      fake::release_for_good();
+      return rc != 0;
+    });
+    CHECK(n > 100, "only %ld enqueues", n);
+  }
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const std::string mode = argc > 1 ? argv[1] : "";
+  if (mode == "copies") check_copies();
+  else return 2;
+  CHECK(!fake::dead_accesses, "%d accesses to freed memory", fake::dead_accesses);
+  std::printf("%s: %d errors\n", mode.c_str(), errors);
+  return errors != 0;
+}
