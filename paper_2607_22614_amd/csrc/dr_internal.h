@@ -131,8 +131,10 @@ struct dr_plan {
   // device side (null for a host-only plan)
   int device = -1;
   dr::DevSeg* d_segs = nullptr;
-  // checksum accumulators (ChunkSum) of every tiling, each from its acc0; zero between launches
+  // checksum accumulators (ChunkSum) of every tiling, each from its acc0; zero between launches,
+  // but for a tiling whose latest call failed (sums_dirty: tiling[0], tiling[1], the moments')
   uint64_t* d_acc = nullptr;
+  std::atomic<bool> sums_dirty[3] = {};
 
   // moment path
   void* bounce[2] = {nullptr, nullptr};  // pinned, Bm bytes each
@@ -203,6 +205,12 @@ struct ReshardLaunch reshard_launch(const dr_plan* p, const float* const* src, f
 
 // The checksum accumulators of tiling tl, with chunk c's checksum going to out[c - out_chunk0].
 ChunkSum chunk_sum(const dr_plan* p, const Tiling& tl, dr_checksum* out, uint32_t out_chunk0);
+// A call on tiling tl that failed once a kernel may have run leaves adds in its chunks' slots: it is
+// marked, and the calls that follow clear the slots of their own chunks on their own stream first
+// (clear_sums, ahead of the tile kernel), until one of the whole stream that is not being recorded
+// into a graph has done so.
+void mark_sums(dr_plan* p, const Tiling& tl);
+int clear_sums(dr_plan* p, const Tiling& tl, uint32_t chunk0, uint32_t nchunks, struct ihipStream_t* st, const char* what);
 int check_stage_args(const dr_plan* p, const float* const* shards, const void* dst, const void* cks,
                      const char* what);
 

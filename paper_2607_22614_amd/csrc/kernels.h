@@ -42,6 +42,9 @@ hipError_t launch_stage_relay(const StageLaunch& l, const Reload& r, hipStream_t
 // slots (written by the tile kernels), which are then set back to zero.
 hipError_t launch_chunk_sums(const ChunkSum& cs, uint32_t chunk0, uint32_t nchunks, hipStream_t st);
 
+// Sets n 64-bit words to zero (a kernel rather than a memset, so that a call stays recordable in a graph).
+hipError_t launch_zero_words(uint64_t* p, uint64_t n, hipStream_t st);
+
 // Reshard kernel over tiles [tile0, tile0 + ntiles).  Destination element e goes to
 // flat[e - flat_bias] when flat is set, else to dst[e / dst_shard_elems]; each
 // tile adds its checksum sums into sum's accumulators (ChunkSum).

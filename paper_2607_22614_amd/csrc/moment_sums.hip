@@ -111,11 +111,17 @@ extern "C" int dr_moment_checksums(dr_plan* p, const float* const* m_shards, con
     args.pieces[w] = m_shards[w];
     args.pieces[W + w] = v_shards[w];
   }
+  const uint32_t n = (uint32_t)p->info.num_moment_chunks;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (int rc = clear_sums(p, tl, 0, n, st, what)) return rc;
   hipLaunchKernelGGL(moment_sum_kernel, dim3(std::min(args.ntiles, kMaxGrid)), dim3(kThreads), 0, st, args);
   e = hipGetLastError();
-  if (e != hipSuccess) return fail(DR_EHIP, "%s: kernel launch: %s", what, hipGetErrorString(e));
-  e = launch_chunk_sums(args.sum, 0, (uint32_t)p->info.num_moment_chunks, st);
-  if (e != hipSuccess) return fail(DR_EHIP, "%s: chunk sum launch: %s", what, hipGetErrorString(e));
-  return DR_OK;
+  const char* step = "kernel launch";
+  if (e == hipSuccess) {
+    step = "chunk sum launch";
+    e = launch_chunk_sums(args.sum, 0, n, st);
+  }
+  if (e == hipSuccess) return DR_OK;
+  mark_sums(p, tl);
+  return fail(DR_EHIP, "%s: %s: %s", what, step, hipGetErrorString(e));
 }

@@ -52,14 +52,6 @@ int scratch_on(int dev, uint64_t** out) {
   return DR_OK;
 }
 
-namespace {
-
-// Sets n 64-bit words to zero (a kernel rather than a memset, so the call stays recordable in a graph).
-__global__ __launch_bounds__(256) void zero_words(uint64_t* p, uint32_t n) {
-  for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) p[i] = 0;
-}
-
-}  // namespace
 }  // namespace dr
 
 using namespace dr;
@@ -90,9 +82,7 @@ extern "C" int dr_stage_chunk_noalloc(dr_plan* p, uint64_t chunk, const float* c
   hipStream_t st = static_cast<hipStream_t>(stream);
   std::atomic<bool>& dirty = g_dirty[p->device];
   if (dirty.load()) {
-    const uint32_t all = (uint32_t)(kScratchBytes / sizeof(uint64_t));
-    hipLaunchKernelGGL(zero_words, dim3((all + 255) / 256), dim3(256), 0, st, ptr, all);
-    const hipError_t e = hipGetLastError();
+    const hipError_t e = launch_zero_words(ptr, kScratchBytes / sizeof(uint64_t), st);
     if (e != hipSuccess) return fail(DR_EHIP, "dr_stage_chunk_noalloc: zero launch: %s", hipGetErrorString(e));
     // a clear recorded into a graph has not run yet: the next eager call clears again
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;

@@ -80,6 +80,10 @@ int create_relay_copies(dr_plan* p) {
   return DR_OK;
 }
 
+int relay_hip(hipError_t e, const char* what, const char* step) {
+  return fail(e == hipErrorOutOfMemory ? DR_ENOMEM : DR_EHIP, "%s: %s: %s", what, step, hipGetErrorString(e));
+}
+
 // Whether kernels on the plan's device can write p: device memory of that device.
 bool kernels_write(const dr_plan* plan, const void* p) {
   hipPointerAttribute_t a{};
@@ -111,7 +115,7 @@ uint64_t packed_before(const dr_plan* p, const Tiling& tl, uint32_t t, uint64_t 
 // nothing) into its chunk's pinned buffer and reloads *prev (null: nothing) from its own.  A buffer
 // is packed again two chunks later, at least one launch after its last piece was reloaded.
 template <typename Launch>
-int relay_kernels(dr_plan* p, const Tiling& tl, uint32_t elem_bytes, uint32_t tile_bytes, Launch launch) {
+int relay_pieces(dr_plan* p, const Tiling& tl, uint32_t elem_bytes, uint32_t tile_bytes, Launch launch) {
   const uint32_t most = std::max<uint32_t>(1, kRelayPieceBytes / tile_bytes);
   Piece prev{};
   bool have = false;
@@ -134,6 +138,22 @@ int relay_kernels(dr_plan* p, const Tiling& tl, uint32_t elem_bytes, uint32_t ti
   return launch(nullptr, &prev);
 }
 
+// The same, and the checksums behind the last launch.
+template <typename Launch>
+int relay_kernels(dr_plan* p, hipStream_t st, const char* what, const ChunkSum& cs, const Tiling& tl,
+                  uint32_t elem_bytes, uint32_t tile_bytes, Launch launch) {
+  const uint32_t n = (uint32_t)p->info.num_chunks;
+  int rc = clear_sums(p, tl, 0, n, st, what);
+  if (rc) return rc;
+  rc = relay_pieces(p, tl, elem_bytes, tile_bytes, launch);
+  if (rc == DR_OK) {
+    const hipError_t e = launch_chunk_sums(cs, 0, n, st);
+    if (e != hipSuccess) rc = relay_hip(e, what, "chunk sum launch");
+  }
+  if (rc) mark_sums(p, tl);
+  return rc;
+}
+
 // Takes the plan's relay buffers for one call; released when the call returns.
 struct RelayHeld {
   dr_plan* p = nullptr;
@@ -154,10 +174,6 @@ struct RelayHeld {
     return DR_OK;
   }
 };
-
-int relay_hip(hipError_t e, const char* what, const char* step) {
-  return fail(e == hipErrorOutOfMemory ? DR_ENOMEM : DR_EHIP, "%s: %s: %s", what, step, hipGetErrorString(e));
-}
 
 // Refuses a stream that is being captured (a graph's replays would share the pinned buffers with the
 // plan's other calls in no order), before anything is allocated or enqueued.
@@ -262,7 +278,7 @@ extern "C" int dr_stage_through_host(dr_plan* p, const float* const* shards, voi
           });
     const Tiling& tl = chunk_launch_tiling(p);
     const ChunkSum cs = chunk_sum(p, tl, d_cks, 0);
-    const int rc = relay_kernels(p, tl, 2, 2048 * tl.depth, [&](const Piece* pack, const Piece* reload) {
+    const int rc = relay_kernels(p, st, what, cs, tl, 2, 2048 * tl.depth, [&](const Piece* pack, const Piece* reload) {
       StageLaunch l = stage_launch(p, tl, shards, cs);
       if (pack) {
         l.dst = p->relay_pin[pack->c & 1];
@@ -279,10 +295,8 @@ extern "C" int dr_stage_through_host(dr_plan* p, const float* const* shards, voi
       const hipError_t e = launch_stage_relay(l, r, st);
       return e == hipSuccess ? DR_OK : relay_hip(e, what, "relay kernel launch");
     });
-    if (rc) return rc;
-    p->last_depth.store(tl.depth, std::memory_order_relaxed);
-    const hipError_t e = launch_chunk_sums(cs, 0, (uint32_t)n, st);
-    return e == hipSuccess ? DR_OK : relay_hip(e, what, "chunk sum launch");
+    if (rc == DR_OK) p->last_depth.store(tl.depth, std::memory_order_relaxed);
+    return rc;
   });
 }
 
@@ -312,7 +326,7 @@ extern "C" int dr_reshard_through_host(dr_plan* p, const float* const* src_shard
           });
     const Tiling& tl = p->tiling[0];
     const ChunkSum cs = chunk_sum(p, tl, d_cks, 0);
-    const int rc = relay_kernels(p, tl, 4, 4096 * tl.depth, [&](const Piece* pack, const Piece* reload) {
+    return relay_kernels(p, st, what, cs, tl, 4, 4096 * tl.depth, [&](const Piece* pack, const Piece* reload) {
       ReshardLaunch l = reshard_launch(p, src_shards, dst_shards, cs);
       if (pack) {
         l.flat = static_cast<float*>(p->relay_pin[pack->c & 1]);
@@ -329,8 +343,5 @@ extern "C" int dr_reshard_through_host(dr_plan* p, const float* const* src_shard
       const hipError_t e = launch_reshard_relay(l, r, st);
       return e == hipSuccess ? DR_OK : relay_hip(e, what, "relay kernel launch");
     });
-    if (rc) return rc;
-    const hipError_t e = launch_chunk_sums(cs, 0, (uint32_t)p->info.num_chunks, st);
-    return e == hipSuccess ? DR_OK : relay_hip(e, what, "chunk sum launch");
   });
 }

@@ -53,16 +53,21 @@ namespace {
 int launch_reshard(dr_plan* p, uint32_t tile0, uint32_t ntiles, const float* const* src, float* const* dst,
                    float* flat, uint64_t flat_bias, uint32_t chunk0, uint32_t nchunks, dr_checksum* cks,
                    hipStream_t st, const char* what) {
+  if (int rc = clear_sums(p, p->tiling[0], chunk0, nchunks, st, what)) return rc;
   ReshardLaunch l = reshard_launch(p, src, dst, chunk_sum(p, p->tiling[0], cks, chunk0));
   l.tile0 = tile0;
   l.ntiles = ntiles;
   l.flat = flat;
   l.flat_bias = flat_bias;
   hipError_t e = launch_reshard_kernel(l, st);
-  if (e != hipSuccess) return fail(DR_EHIP, "%s: kernel launch: %s", what, hipGetErrorString(e));
-  e = launch_chunk_sums(l.sum, chunk0, nchunks, st);
-  if (e != hipSuccess) return fail(DR_EHIP, "%s: chunk sum launch: %s", what, hipGetErrorString(e));
-  return DR_OK;
+  const char* step = "kernel launch";
+  if (e == hipSuccess) {
+    step = "chunk sum launch";
+    e = launch_chunk_sums(l.sum, chunk0, nchunks, st);
+  }
+  if (e == hipSuccess) return DR_OK;
+  mark_sums(p, p->tiling[0]);
+  return fail(DR_EHIP, "%s: %s: %s", what, step, hipGetErrorString(e));
 }
 
 }  // namespace

@@ -355,7 +355,18 @@ __global__ __launch_bounds__(kThreads) void chunk_sum_kernel(ChunkSum cs, uint32
   }
 }
 
+__global__ __launch_bounds__(kThreads) void zero_words_kernel(uint64_t* p, uint64_t n) {
+  for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (uint64_t)gridDim.x * kThreads) p[i] = 0;
+}
+
 }  // namespace
+
+hipError_t launch_zero_words(uint64_t* p, uint64_t n, hipStream_t st) {
+  if (!n) return hipSuccess;
+  const uint32_t grid = (uint32_t)std::min<uint64_t>((n + kThreads - 1) / kThreads, kMaxSumGrid);
+  hipLaunchKernelGGL(zero_words_kernel, dim3(grid), dim3(kThreads), 0, st, p, n);
+  return hipGetLastError();
+}
 
 hipError_t launch_chunk_sums(const ChunkSum& cs, uint32_t chunk0, uint32_t nchunks, hipStream_t st) {
   if (!nchunks) return hipSuccess;

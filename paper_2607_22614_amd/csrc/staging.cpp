@@ -108,7 +108,15 @@ int launch(dr_plan* p, const Tiling& tl, uint32_t tile0, uint32_t ntiles, const 
 // Chunk `chunk` with tiling tl into dst_chunk, its checksum into *ck.
 int launch_one_chunk(dr_plan* p, const Tiling& tl, uint64_t chunk, const float* const* shards, void* dst_chunk,
                      dr_checksum* ck, hipStream_t st, const char* what) {
-  return launch_chunk_into(p, tl, chunk, shards, dst_chunk, chunk_sum(p, tl, ck, (uint32_t)chunk), st, what);
+  int rc = clear_sums(p, tl, (uint32_t)chunk, 1, st, what);
+  if (rc) return rc;
+  rc = launch_chunk_into(p, tl, chunk, shards, dst_chunk, chunk_sum(p, tl, ck, (uint32_t)chunk), st, what);
+  if (rc) mark_sums(p, tl);
+  return rc;
+}
+
+std::atomic<bool>& sums_dirty(dr_plan* p, const Tiling& tl) {
+  return p->sums_dirty[&tl == &p->tiling[0] ? 0 : &tl == &p->tiling[1] ? 1 : 2];
 }
 
 uint64_t chunk_out_bytes(const dr_plan* p, uint64_t chunk) {
@@ -147,6 +155,21 @@ ChunkSum chunk_sum(const dr_plan* p, const Tiling& tl, dr_checksum* out, uint32_
   cs.out_chunk0 = out_chunk0;
   cs.chunk_bias = 0;
   return cs;
+}
+
+void mark_sums(dr_plan* p, const Tiling& tl) { sums_dirty(p, tl) = true; }
+
+int clear_sums(dr_plan* p, const Tiling& tl, uint32_t chunk0, uint32_t nchunks, hipStream_t st, const char* what) {
+  if (!sums_dirty(p, tl).load(std::memory_order_relaxed)) return DR_OK;
+  const uint64_t words = (uint64_t)tl.sum_slots * tl.sum_stride;
+  const hipError_t e = launch_zero_words(p->d_acc + tl.acc0 + chunk0 * words, nchunks * words, st);
+  if (e != hipSuccess) return fail(DR_EHIP, "%s: clear launch: %s", what, hipGetErrorString(e));
+  // a clear recorded into a graph has not run yet
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (nchunks + 1 == tl.chunk_tile_begin.size() && hipStreamIsCapturing(st, &capture) == hipSuccess &&
+      capture == hipStreamCaptureStatusNone)
+    sums_dirty(p, tl) = false;
+  return DR_OK;
 }
 
 StageLaunch stage_launch(const dr_plan* p, const Tiling& tl, const float* const* shards, const ChunkSum& cs) {
@@ -265,9 +288,13 @@ extern "C" int dr_stage_all(dr_plan* p, const float* const* shards, void* dst, d
   const int pick = pick_tiling(p);
   const Tiling& tl = p->tiling[pick];
   const uint64_t bytes = 4 * p->info.n_elems + p->info.rollout_bytes;
-  const int rc = launch(p, tl, 0, (uint32_t)tl.tiles.size(), shards, dst, 0, 0, (uint32_t)p->info.num_chunks,
-                        bytes <= (pick == 1 ? kGroupedLoneBytes : kGroupedBytes), chunk_sum(p, tl, d_cks, 0),
-                        static_cast<hipStream_t>(stream), "dr_stage_all");
+  const uint32_t n = (uint32_t)p->info.num_chunks;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (int rc = clear_sums(p, tl, 0, n, st, "dr_stage_all")) return rc;
+  const int rc = launch(p, tl, 0, (uint32_t)tl.tiles.size(), shards, dst, 0, 0, n,
+                        bytes <= (pick == 1 ? kGroupedLoneBytes : kGroupedBytes), chunk_sum(p, tl, d_cks, 0), st,
+                        "dr_stage_all");
   if (rc == DR_OK) note_pack(p, bytes);
+  else mark_sums(p, tl);
   return rc;
 }

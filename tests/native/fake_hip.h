@@ -43,6 +43,7 @@ inline Stream null_stream;
 inline std::vector<std::unique_ptr<Stream>> streams;
 inline std::map<char*, Alloc> allocs;
 inline long enqueues = 0, fail_at = 0;  // fail_at: which enqueue fails, counted from 1; 0: none
+inline bool fail_late = false;          // a launch that fails is enqueued all the same (an older error reported late)
 inline int dead_accesses = 0;           // work that ran on memory already freed
 
 inline Stream* of(hipStream_t s) { return s ? reinterpret_cast<Stream*>(s) : &null_stream; }
@@ -71,9 +72,9 @@ inline void drain_all(int device) {
 inline bool failing() { return ++enqueues == fail_at; }
 
 inline hipError_t launch(hipStream_t s, std::function<void()> f) {
-  if (failing()) return hipErrorUnknown;
-  of(s)->ops.push_back(Op{std::move(f), nullptr, nullptr});
-  return hipSuccess;
+  const bool fails = failing();
+  if (!fails || fail_late) of(s)->ops.push_back(Op{std::move(f), nullptr, nullptr});
+  return fails ? hipErrorUnknown : hipSuccess;
 }
 
 inline Alloc* find(const void* p) {

@@ -1,7 +1,7 @@
 // The library's host code (plans, launches, the paths through host memory) on the CPU, over the
 // stand-in runtime of fake_hip.h and plain loops in place of the kernels: what is enqueued, in what
 // order, and what is left behind when a call fails or a plan goes away.
-//   host_check copies|sums|destroy
+//   host_check copies|sums
 // Exit status 0 when everything holds.
 #include "fake_hip.h"
 
@@ -123,13 +123,13 @@ void reshard_tiles(const ReshardLaunch& l, const std::vector<const float*>& src,
 int scratch_on(int, uint64_t** out) { return *out = nullptr, DR_OK; }
 
 hipError_t launch_stage_kernel(const StageLaunch& l, hipStream_t st) {
-  launched.push_back({l.ntiles, 0, false, l.grouped, l.depth});
+  if (launched.size() < 10000) launched.push_back({l.ntiles, 0, false, l.grouped, l.depth});
   std::vector<const float*> shards(l.shards, l.shards + l.num_shards);
   return fake::launch(st, [=] { stage_tiles(l, shards); });
 }
 
 hipError_t launch_stage_relay(const StageLaunch& l, const Reload& r, hipStream_t st) {
-  launched.push_back({l.ntiles, r.groups, true, l.grouped, l.depth});
+  if (launched.size() < 10000) launched.push_back({l.ntiles, r.groups, true, l.grouped, l.depth});
   std::vector<const float*> shards(l.shards, l.shards + l.num_shards);
   return fake::launch(st, [=] {  // the reload first or last: the launch leaves it open
     const bool first = l.tile0 & 1;
@@ -151,6 +151,13 @@ hipError_t launch_chunk_sums(const ChunkSum& cs, uint32_t chunk0, uint32_t n, hi
   });
 }
 
+hipError_t launch_zero_words(uint64_t* p, uint64_t n, hipStream_t st) {
+  return fake::launch(st, [=] {
+    fake::touch(p);
+    std::memset(p, 0, 8 * n);
+  });
+}
+
 hipError_t launch_reshard_kernel(const ReshardLaunch& l, hipStream_t st) {
   std::vector<const float*> src(l.src, l.src + l.num_src);
   std::vector<float*> dst;
@@ -159,7 +166,7 @@ hipError_t launch_reshard_kernel(const ReshardLaunch& l, hipStream_t st) {
 }
 
 hipError_t launch_reshard_relay(const ReshardLaunch& l, const Reload& r, hipStream_t st) {
-  launched.push_back({l.ntiles, r.groups, true, false, 0});
+  if (launched.size() < 10000) launched.push_back({l.ntiles, r.groups, true, false, 0});
   std::vector<const float*> src(l.src, l.src + l.num_src);
   std::vector<float*> dst(l.dst, l.dst + l.num_dst);
   return fake::launch(st, [=] {
@@ -283,11 +290,61 @@ void check_copies() {
   }
 }
 
+// After a call that failed anywhere, the plan's later calls write the right checksums, and once a
+// whole-stream call has run they enqueue no more than before the failure.
+void check_sums() {
+  enum { kAll, kChunk, kHost };
+  const auto call = [](Work& k, int op, hipStream_t st) -> int {
+    if (op == kHost) return k.through_host(k.dst, st);
+    if (op == kAll || k.p->kind != kRollout) return k.all(st);
+    for (uint64_t c = 0; c < k.p->info.num_chunks; ++c)
+      if (int rc = dr_stage_chunk(k.p, c, k.src.data(), k.dst + c * k.p->layout.chunk_bytes, k.cks + c, st)) return rc;
+    return DR_OK;
+  };
+  for (int late = 0; late < 2; ++late)
+    for (int to : {3, -2})
+      for (int depth : {2, 0})
+        for (int op : {kAll, kChunk, kHost}) {
+          if (to < 0 && (op == kChunk || depth)) continue;
+          // chunks of few tiles (packed slots), and of enough to sum themselves
+          for (uint64_t chunk : {4096u, 48u << 10}) {
+            long before = 0;
+            each_failure([&](long i) {
+              Work k = setup(kSmall, 4, to, chunk, depth);
+              fake::enqueues = 0;
+              CHECK(!call(k, op, nullptr), "%s", dr_last_error());
+              before = fake::enqueues;
+              (void)hipDeviceSynchronize();
+              const hipStream_t st = stream(), st2 = stream();
+              fake::fail_late = late;
+              const int rc = failing_call(i, [&] { return call(k, op, st); });
+              fake::fail_late = false;
+              const int after[] = {op, kChunk, kHost, kAll, op};
+              for (int j = 0; j < 5; ++j) {
+                (void)hipDeviceSynchronize();
+                k.clear();
+                fake::enqueues = 0;
+                CHECK(!call(k, after[j], j & 1 ? st2 : st), "%s", dr_last_error());
+                const long n = fake::enqueues;
+                (void)hipDeviceSynchronize();
+                CHECK(k.right(k.dst), "to %d, op %d, enqueue %ld failed, then call %d", to, op, i, j);
+                // (an automatic plan has two tilings, each cleared by its own whole-stream call)
+                CHECK(j < 4 || n <= before || (depth == 0 && to > 0), "%ld enqueues, %ld before", n, before);
+              }
+              dr_plan_destroy(k.p);
+              fake::release_for_good();
+              return rc != 0;
+            });
+          }
+        }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::string mode = argc > 1 ? argv[1] : "";
   if (mode == "copies") check_copies();
+  else if (mode == "sums") check_sums();
   else return 2;
   CHECK(!fake::dead_accesses, "%d accesses to freed memory", fake::dead_accesses);
   std::printf("%s: %d errors\n", mode.c_str(), errors);
