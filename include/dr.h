@@ -230,8 +230,8 @@ int dr_plan_create(const dr_model* model, const dr_layout* layout, dr_plan** out
 int dr_plan_create_host(const dr_model* model, const dr_layout* layout, dr_plan** out);
 
 /* Frees the plan's device tables and pinned buffers.  The caller must have
- * synchronized every stream that still uses the plan (the plan's own copy
- * streams and a deferred restore are waited for here).  NULL is a no-op. */
+ * synchronized every stream that still uses the plan (calls through host
+ * memory and a deferred restore are waited for here).  NULL is a no-op. */
 void dr_plan_destroy(dr_plan* plan);
 
 /* Sizes and counts of the plan (dr_plan_info), and the tile depth of its
@@ -314,8 +314,8 @@ int dr_stage_all(dr_plan* plan, const float* const* shards, void* dst, dr_checks
  *   stream: hipStream_t running the kernels; it also waits for those copies,
  *   so results are valid once the stream has reached this point.  Does not
  *   block the calling thread.  Calls on one plan are ordered by the plan's
- *   events; the plan must outlive the enqueued work (dr_plan_destroy
- *   synchronizes the device).  Cannot be recorded into a HIP graph.
+ *   events; the plan must outlive the enqueued work (dr_plan_destroy waits
+ *   for the latest call).  Cannot be recorded into a HIP graph.
  * Errors: DR_EINVAL (as dr_stage_all), DR_ENOMEM, DR_EHIP (the stream is being
  * captured, among others). */
 int dr_stage_through_host(dr_plan* plan, const float* const* shards, void* dst, dr_checksum* d_cks, void* stream);

@@ -28,7 +28,8 @@ namespace dr {
 
 void free_relay_resources(dr_plan* p) {
   if (p->relay_stream) (void)hipStreamSynchronize(static_cast<hipStream_t>(p->relay_stream));
-  if (p->relay_pin[0]) (void)hipDeviceSynchronize();  // kernels writing the pinned buffers
+  // the latest call's kernels, and with them every earlier call's, whatever device is current now
+  if (p->relay_ev[4]) (void)hipEventSynchronize(static_cast<hipEvent_t>(p->relay_ev[4]));
   for (int i = 0; i < 5; ++i) {
     if (p->relay_ev[i]) (void)hipEventDestroy(static_cast<hipEvent_t>(p->relay_ev[i]));
     p->relay_ev[i] = nullptr;

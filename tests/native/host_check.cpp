@@ -1,7 +1,7 @@
 // The library's host code (plans, launches, the paths through host memory) on the CPU, over the
 // stand-in runtime of fake_hip.h and plain loops in place of the kernels: what is enqueued, in what
 // order, and what is left behind when a call fails or a plan goes away.
-//   host_check copies|sums
+//   host_check copies|sums|destroy
 // Exit status 0 when everything holds.
 #include "fake_hip.h"
 
@@ -339,12 +339,42 @@ void check_sums() {
         }
 }
 
+// The pinned buffers outlive the work of the latest call when the plan goes away, whatever device is
+// current, and when the copy stream of a later call cannot be made.
+void check_destroy() {
+  for (int to : {3, -2})
+    for (bool copies : {false, true}) {
+      Work k = setup(kSmall, 4, to, 4096);
+      CHECK(!k.through_host(copies ? k.pinned : k.dst, stream()), "%s", dr_last_error());
+      (void)hipSetDevice(1);
+      dr_plan_destroy(k.p);
+      (void)hipSetDevice(0);
+      (void)hipDeviceSynchronize();
+      CHECK(k.right(copies ? k.pinned : k.dst), "plan destroyed with device 1 current");
+      fake::release_for_good();
+    }
+  for (long i = 1; i <= 8; ++i) {
+    Work k = setup(kSmall, 4, 3, 4096);
+    CHECK(!k.through_host(k.dst, stream()), "%s", dr_last_error());
+    (void)failing_call(i, [&] { return k.through_host(k.pinned, stream()); });
+    (void)hipDeviceSynchronize();
+    CHECK(!std::memcmp(k.dst, k.want.data(), k.want.size()), "the first call, enqueue %ld of the second failed", i);
+    k.clear();
+    CHECK(!k.through_host(k.dst, stream()), "%s", dr_last_error());
+    (void)hipDeviceSynchronize();
+    CHECK(k.right(k.dst), "after enqueue %ld failed", i);
+    dr_plan_destroy(k.p);
+    fake::release_for_good();
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::string mode = argc > 1 ? argv[1] : "";
   if (mode == "copies") check_copies();
   else if (mode == "sums") check_sums();
+  else if (mode == "destroy") check_destroy();
   else return 2;
   CHECK(!fake::dead_accesses, "%d accesses to freed memory", fake::dead_accesses);
   std::printf("%s: %d errors\n", mode.c_str(), errors);
