@@ -33,16 +33,20 @@ int check_device(const dr_plan* p, const char* what) {
 // Tile order of a launch.  A short launch is mostly its start, when nothing of source, destination
 // and tables has been touched for a while: in grouped order the chip works on one window of 512
 // tiles, in contiguous order on eight places of the stream at once.  Once the launch runs, contiguous
-// order is the faster one.  Measured contiguous / grouped by 64 tiles:
-//   one chunk a launch (loops of them): 20 of 64 MiB (0.5B) 732 / 687 us, 60 of 256 MiB (8B) 7.82 / 7.73
-//   ms (groups of 4-32 and 128-256 tiles: 686-732 us, 7.82-8.09 ms): grouped;
-//   whole streams behind another pack, by GB moved: 0.2 34.3 / 33.1 us, 0.4 62.2 / 59.8, 0.5 88.9 /
-//   85.1, 0.7 115.5 / 110.8, 1.1 172.6 / 171.3, 1.4 213 / 217, 3.8 571 / 580, 48 7312 / 7457: grouped up
-//   to kGroupedBytes;
-//   whole streams after 30 ms idle (the deep tiling): 0.5 218 / 203 us, 1.8 379 / 355, 3.8 638 / 635, 16
-//   2730 / 2780, 48 7550 / 7660: grouped up to kGroupedLoneBytes.
-constexpr uint64_t kGroupedBytes = 1ull << 30;
-constexpr uint64_t kGroupedLoneBytes = 4ull << 30;
+// order is the faster one.  The line depends on the depth, not on what ran before the launch or
+// which call makes it.  Grouped against contiguous, back to back / after 30 ms idle, GiB read and
+// written, decoders of six widths:
+//   depth 2, whole streams: 0.3-0.9 -1..-5 % / -0..-3; 1.2-2.5 -0..-4 / +1..-3; 3.5-4.5 +0..-3 / +1..-3;
+//   5-5.5 +1..-3 / +2..-3; 6.5 +1..-2; 16-45 +2 / +1;
+//   depth 4, whole streams: 0.3-0.5 -2..-4 %; 0.8-2.3 0..-2; 3.9-6.6 -0..-2 / -0..-2 in twelve of
+//   thirteen; 7-8 0; 11-16 +1; 45 +1.5 / +1.5;
+//   depth 4, one chunk a launch: 0.2 -8 %, 0.8 -1.4, 3 -2, 6 -1.2, 12 +0.4, 24 +1.1, 45 +1.5 / +1.2.
+constexpr uint64_t kGroupedBytes = 3ull << 30;
+constexpr uint64_t kGroupedDeepBytes = 6ull << 30;
+
+bool grouped_order(int depth, uint64_t bytes) {
+  return bytes <= (depth == kVecItersLarge ? kGroupedDeepBytes : kGroupedBytes);
+}
 
 // Per-device state of the automatic tile depth (see pack_drain_ns in the
 // internal header): when the packs launched so far should have drained.
@@ -84,17 +88,17 @@ bool own_sums(const Tiling& tl, uint32_t ntiles, hipStream_t st) {
   return capture == hipStreamCaptureStatusNone;
 }
 
-// Tiles [tile0, tile0 + ntiles) of tiling tl, which cover chunks [chunk0, chunk0 + nchunks), then
-// their checksums from the accumulators of cs.
+// Tiles [tile0, tile0 + ntiles) of tiling tl, which cover chunks [chunk0, chunk0 + nchunks) and move
+// `bytes` in all, then their checksums from the accumulators of cs.
 int launch(dr_plan* p, const Tiling& tl, uint32_t tile0, uint32_t ntiles, const float* const* shards, void* dst,
-           uint64_t dst_bias, uint32_t chunk0, uint32_t nchunks, bool grouped, const ChunkSum& cs, hipStream_t st,
+           uint64_t dst_bias, uint32_t chunk0, uint32_t nchunks, uint64_t bytes, const ChunkSum& cs, hipStream_t st,
            const char* what) {
   StageLaunch l = stage_launch(p, tl, shards, cs);
   l.dst = dst;
   l.dst_bias = dst_bias;
   l.tile0 = tile0;
   l.ntiles = ntiles;
-  l.grouped = grouped;
+  l.grouped = grouped_order(tl.depth, bytes);
   if (own_sums(tl, ntiles, st)) l.sum.chunk_tiles = tl.d_chunk_tile_begin;
   hipError_t e = launch_stage_kernel(l, st);
   if (e != hipSuccess) return fail(DR_EHIP, "%s: stage kernel launch: %s", what, hipGetErrorString(e));
@@ -196,8 +200,8 @@ int check_stage_args(const dr_plan* p, const float* const* shards, const void* d
 int launch_chunk_into(dr_plan* p, const Tiling& tl, uint64_t chunk, const float* const* shards, void* dst_chunk,
                       const ChunkSum& cs, hipStream_t st, const char* what) {
   const uint32_t t0 = tl.chunk_tile_begin[chunk], t1 = tl.chunk_tile_begin[chunk + 1];
-  return launch(p, tl, t0, t1 - t0, shards, dst_chunk, chunk * (p->layout.chunk_bytes / 2), (uint32_t)chunk, 1, true,
-                cs, st, what);
+  return launch(p, tl, t0, t1 - t0, shards, dst_chunk, chunk * (p->layout.chunk_bytes / 2), (uint32_t)chunk, 1,
+                3 * chunk_out_bytes(p, chunk), cs, st, what);
 }
 
 const Tiling& chunk_launch_tiling(const dr_plan* p) { return p->tiling[chunk_tiling(p)]; }
@@ -285,15 +289,13 @@ extern "C" int dr_stage_all(dr_plan* p, const float* const* shards, void* dst, d
   if (!aligned16(d_cks)) return fail(DR_EINVAL, "dr_stage_all: d_cks is null or not 16-byte aligned");
   if (!p->d_segs) return fail(DR_EINVAL, "dr_stage_all: host-only plan has no device tables");
   if (int rc = check_device(p, "dr_stage_all")) return rc;
-  const int pick = pick_tiling(p);
-  const Tiling& tl = p->tiling[pick];
+  const Tiling& tl = p->tiling[pick_tiling(p)];
   const uint64_t bytes = 4 * p->info.n_elems + p->info.rollout_bytes;
   const uint32_t n = (uint32_t)p->info.num_chunks;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (int rc = clear_sums(p, tl, 0, n, st, "dr_stage_all")) return rc;
-  const int rc = launch(p, tl, 0, (uint32_t)tl.tiles.size(), shards, dst, 0, 0, n,
-                        bytes <= (pick == 1 ? kGroupedLoneBytes : kGroupedBytes), chunk_sum(p, tl, d_cks, 0), st,
-                        "dr_stage_all");
+  const int rc = launch(p, tl, 0, (uint32_t)tl.tiles.size(), shards, dst, 0, 0, n, bytes, chunk_sum(p, tl, d_cks, 0),
+                        st, "dr_stage_all");
   if (rc == DR_OK) note_pack(p, bytes);
   else mark_sums(p, tl);
   return rc;

@@ -1,7 +1,7 @@
 // The library's host code (plans, launches, the paths through host memory) on the CPU, over the
 // stand-in runtime of fake_hip.h and plain loops in place of the kernels: what is enqueued, in what
 // order, and what is left behind when a call fails or a plan goes away.
-//   host_check copies|sums|destroy
+//   host_check copies|sums|destroy|order
 // Exit status 0 when everything holds.
 #include "fake_hip.h"
 
@@ -368,6 +368,36 @@ void check_destroy() {
   }
 }
 
+// The tile order follows a launch's depth and traffic, whichever call makes it: grouped up to 3 GiB
+// at depth 2 and up to 6 GiB at depth 4.  The launches are only recorded, nothing runs.
+void check_order() {
+  const struct { int32_t vocab; double gib; } sizes[] = {  // one chunk; GiB read and written
+      {2000, 0.1}, {20000, 0.9}, {60000, 2.7}, {80000, 3.7}, {120000, 5.5}, {140000, 6.5}, {200000, 9.2}};
+  for (const auto& z : sizes)
+    for (int depth : {0, 2, 4}) {
+      const dr_model m{0, 4096, 32, 8, 128, 14336, z.vocab};
+      const dr_layout l{1, 1, 1ull << 40, 0, depth, 0};
+      dr_plan* p;
+      CHECK(!dr_plan_create(&m, &l, &p), "%s", dr_last_error());
+      const uint64_t bytes = 4 * p->info.n_elems + p->info.rollout_bytes;
+      CHECK(std::abs(bytes / 1073741824.0 - z.gib) < 0.1, "%.2f GiB", bytes / 1073741824.0);
+      float* src = reinterpret_cast<float*>(4096);  // never read
+      dr_checksum* cks = reinterpret_cast<dr_checksum*>(4096);
+      for (int chunk = 0; chunk < 2; ++chunk) {
+        launched.clear();
+        const int rc = chunk ? dr_stage_chunk(p, 0, &src, src, cks, nullptr) : dr_stage_all(p, &src, src, cks, nullptr);
+        CHECK(!rc && launched.size() == 1, "%s", dr_last_error());
+        const StageRecord& r = launched.back();
+        CHECK(!depth || r.depth == depth, "depth %d", r.depth);
+        CHECK(r.grouped == (z.gib < (r.depth == 4 ? 6 : 3)), "%.1f GiB, depth %d, chunk call %d: grouped %d", z.gib, r.depth,
+              chunk, r.grouped);
+      }
+      fake::null_stream.ops.clear();
+      dr_plan_destroy(p);
+      fake::release_for_good();
+    }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -375,6 +405,7 @@ int main(int argc, char** argv) {
   if (mode == "copies") check_copies();
   else if (mode == "sums") check_sums();
   else if (mode == "destroy") check_destroy();
+  else if (mode == "order") check_order();
   else return 2;
   CHECK(!fake::dead_accesses, "%d accesses to freed memory", fake::dead_accesses);
   std::printf("%s: %d errors\n", mode.c_str(), errors);

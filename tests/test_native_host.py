@@ -28,7 +28,7 @@ def host_check(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("mode", ["copies", "sums", "destroy"])
+@pytest.mark.parametrize("mode", ["copies", "sums", "destroy", "order"])
 def test_host_code(host_check, mode):
     r = subprocess.run([host_check, mode], capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, r.stdout + r.stderr
