@@ -55,6 +55,7 @@ struct ReshardLaunch {
   uint64_t chunk_elems;      // B / 4
   uint64_t dst_shard_elems;  // S'
   uint32_t tile0, ntiles;
+  bool whole_tiles;          // a workgroup moves a whole tile, each XCD a contiguous eighth of them
   float* flat;
   uint64_t flat_bias;
   int num_src;

@@ -47,6 +47,11 @@ ReshardLaunch reshard_launch(const dr_plan* p, const float* const* src, float* c
 
 namespace {
 
+// Reshards that read and write more than this move whole tiles per workgroup, smaller ones half tiles:
+// at 43 GB (40.3 GiB) halves are 1-2 % faster, at 50 GB (46.9 GiB) whole tiles 0.5-1 %, at 57 GB 1.5 %
+// (the table at the kernel).
+constexpr uint64_t kWholeTileBytes = 44ull << 30;
+
 // Tiles [tile0, tile0 + ntiles) of a reshard plan; flat (if not null) receives the destination
 // elements from flat_bias on instead of the destination shards.  The tiles cover chunks
 // [chunk0, chunk0 + nchunks); the checksum of chunk c goes to cks[c - chunk0].
@@ -59,6 +64,7 @@ int launch_reshard(dr_plan* p, uint32_t tile0, uint32_t ntiles, const float* con
   l.ntiles = ntiles;
   l.flat = flat;
   l.flat_bias = flat_bias;
+  l.whole_tiles = !flat && 4 * p->info.n_elems + p->info.rollout_bytes > kWholeTileBytes;
   hipError_t e = launch_reshard_kernel(l, st);
   const char* step = "kernel launch";
   if (e == hipSuccess) {

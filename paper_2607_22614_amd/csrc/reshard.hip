@@ -80,19 +80,32 @@ __device__ __forceinline__ void reshard_tile(const ReshardArgs& a, uint32_t g, u
   if (threadIdx.x == 0) add_tile_sums(a.sum, g, s.chunk, acc_w, (pos0 + 1) * acc_w + acc_rw);
 }
 
-// A workgroup moves half a tile, two 16-byte groups per lane, and the XCDs take groups of 32 halves
-// (256 KiB) in turn.  Bound by HBM, where the read and the write stream meet in the same banks:
-// how they fall together depends on the tile's size, on the order and on where the buffers lie.
-// The 8B shape at 16 layers, 8 to 6 shards (36.3 GB), back to back / after 50 ms idle, when the clock
-// is lower: whole tiles per workgroup, each XCD on its own eighth of the stream 5.87 / 5.93 ms;
-// halves in that order 5.69-6.03 / 6.10; halves in groups of 16 / 32 / 64 / 256: 5.86 / 5.63 / 5.84
-// / 5.80 (32: 5.75 after idle); quarters in groups of 64 5.59 / 6.16.  At 32 layers 9.83-10.51 /
-// 10.44 before, 9.99-10.18 / 10.11 now; 0.5B 0.830 / 0.881 and 0.797 / 0.857; 5 to 3 shards of an odd
-// width 0.940 / 1.00 and 0.865 / 0.937.
+// kHalves: a workgroup moves half a tile, two 16-byte groups per lane, and the XCDs take groups of 32
+// halves (256 KiB) in turn; else it moves a whole tile and each XCD streams through one eighth.
+// Bound by HBM, where the read and the write stream meet in the same banks: how they fall together
+// depends on the tile's size, on the order and on where the buffers lie.  Mean over five placements
+// of the buffers (+- over the placements) in us, whole / halves, back to back; after 30 ms idle:
+//   0.5B, 8 to 6 shards (5.0 GB)  825+-18 / 790+-3; 861 / 825      odd width, 5 to 3 (5.4)  943+-4 / 877+-15; 975 / 910
+//   8B width, 8 layers, 4 to 16 (22.3)  3651+-16 / 3560+-47; 3678 / 3605
+//   16 layers, 8 to 6 (36.3)  5811+-158 / 5650+-55; 5894 / 5816    20 (43.3)  6882+-230 / 6764+-29; 6931 / 6849
+//   24 layers (50.3)  7818+-158 / 7858+-39; 7876 / 7954            28 (57.2)  8817+-118 / 8946+-30; 8902 / 9056
+//   32 layers (64.2)  9964+-226 / 10090+-19; 10009 / 10223         32, 8 to 3  10094 / 10076; 10186 / 10200
+//   32, 4 to 16  10036 / 10029; 10076 / 10145                      44 (85)  13211+-86 / 13348+-65; 13273 / 13494
+//   32B width, 20 layers (91)  14130 / 14185; 14177 / 14350
+// So halves up to kWholeTileBytes, whole tiles beyond (launch_reshard).  Halves in groups of 16 / 64 /
+// 128 instead of 32 at 16 layers: 5882 / 5700 / 5655, at 32 layers 10602 / 10169 / 10180; halves in
+// contiguous order 5763 and 9931 back to back, but 5993 and 10190 after idle; whole tiles in groups
+// or in plain order 5868-6189 and 10489-11055.
+template <bool kHalves>
 __global__ __launch_bounds__(kThreads) void reshard_kernel(ReshardArgs args) {
   (void)args;  // read through the kernarg segment (same bytes)
   const ReshardArgs& a = *(const ReshardArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   __shared__ uint64_t red[2][kThreads / 64];
+  if (!kHalves) {
+    for (uint32_t b = blockIdx.x; b < a.ntiles; b += gridDim.x)
+      reshard_tile<kReshardIters>(a, a.tile0 + xcd_tile(b, a.ntiles), 0, red);
+    return;
+  }
   const uint64_t n = (uint64_t)a.ntiles << a.part_shift;
   for (uint64_t b = blockIdx.x; b < n; b += gridDim.x) {
     const uint64_t t = xcd_group<kPartGroup>(b, n);
@@ -170,10 +183,14 @@ ReshardArgs reshard_args(const ReshardLaunch& l) {
 hipError_t launch_reshard_kernel(const ReshardLaunch& l, hipStream_t st) {
   if (!l.ntiles) return hipSuccess;
   ReshardArgs args = reshard_args(l);
+  if (l.whole_tiles) {
+    hipLaunchKernelGGL(reshard_kernel<false>, dim3(std::min(l.ntiles, kMaxGrid)), dim3(kThreads), 0, st, args);
+    return hipGetLastError();
+  }
   // one part where a chunk, and so a tile, holds no more groups than a part
   args.part_shift = l.chunk_elems / 4 <= (uint64_t)kPartIters * kThreads ? 0 : 1;
   const uint64_t grid = std::min<uint64_t>((uint64_t)l.ntiles << args.part_shift, kMaxGrid);
-  hipLaunchKernelGGL(reshard_kernel, dim3((uint32_t)grid), dim3(kThreads), 0, st, args);
+  hipLaunchKernelGGL(reshard_kernel<true>, dim3((uint32_t)grid), dim3(kThreads), 0, st, args);
   return hipGetLastError();
 }
 

@@ -36,6 +36,11 @@ struct StageRecord {  // every stage launch, in order
   int depth;
 };
 std::vector<StageRecord> launched;
+struct ReshardRecord {
+  uint32_t ntiles;
+  bool whole_tiles;
+};
+std::vector<ReshardRecord> resharded;
 
 uint16_t bf16(float x) {  // finite inputs
   uint32_t u;
@@ -159,6 +164,7 @@ hipError_t launch_zero_words(uint64_t* p, uint64_t n, hipStream_t st) {
 }
 
 hipError_t launch_reshard_kernel(const ReshardLaunch& l, hipStream_t st) {
+  resharded.push_back({l.ntiles, l.whole_tiles});
   std::vector<const float*> src(l.src, l.src + l.num_src);
   std::vector<float*> dst;
   if (l.dst) dst.assign(l.dst, l.dst + l.num_dst);
@@ -392,6 +398,20 @@ void check_order() {
         CHECK(r.grouped == (z.gib < (r.depth == 4 ? 6 : 3)), "%.1f GiB, depth %d, chunk call %d: grouped %d", z.gib, r.depth,
               chunk, r.grouped);
       }
+      fake::null_stream.ops.clear();
+      dr_plan_destroy(p);
+      fake::release_for_good();
+    }
+  // whole tiles per workgroup for a reshard of more than 44 GiB, and for chunks of as much
+  for (int32_t vocab : {4000, 60000, 700000, 750000})
+    for (uint64_t chunk : {1ull << 20, 1ull << 40}) {
+      const dr_model m{0, 4096, 32, 8, 128, 14336, vocab};
+      dr_plan* p;
+      CHECK(!dr_reshard_plan_create(&m, 3, 2, chunk, &p), "%s", dr_last_error());
+      float* at[3];
+      for (float*& x : at) x = reinterpret_cast<float*>(4096);
+      CHECK(!dr_reshard(p, at, at, reinterpret_cast<dr_checksum*>(4096), nullptr), "%s", dr_last_error());
+      CHECK(resharded.back().whole_tiles == (vocab == 750000), "vocabulary %d: %d", vocab, resharded.back().whole_tiles);
       fake::null_stream.ops.clear();
       dr_plan_destroy(p);
       fake::release_for_good();

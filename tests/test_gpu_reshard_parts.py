@@ -37,3 +37,27 @@ def test_parts_and_order(b, w, w2):
         got = np.concatenate([d.cpu().numpy().view(np.uint32) for d in dst])
         assert np.array_equal(got, want)
         assert checksums_to_list(cks) == oracle.chunk_checksums(want, b)
+
+
+# more than 44 GiB read and written (a workgroup then moves a whole tile): ragged shards and chunks, and 64 shards
+@pytest.mark.parametrize("w,w2,b,vocab", [(13, 7, (48 << 20) + 16, 725001), (1, 64, 1 << 30, 730001)])
+def test_whole_tiles(w, w2, b, vocab):
+    model = (0, 4096, 32, 8, 128, 14336, vocab)
+    say("reshard whole tiles", model, w, "->", w2, "B", b)
+    plan = dr.dr_reshard_plan_create(model, w, w2, b)
+    info = dr.dr_plan_get_info(plan)
+    assert 4 * info["n_elems"] + info["rollout_bytes"] > 44 << 30
+    n, S, S2 = info["n_elems"], info["shard_elems"], info["dst_shard_elems"]
+    flat = torch.empty(w * S, dtype=torch.int32, device="cuda").random_()
+    src = [flat[i * S:(i + 1) * S] for i in range(w)]
+    out = torch.full((w2 * S2,), -1, dtype=torch.int32, device="cuda")
+    cks = new_checksums(info["num_chunks"])
+    dr.dr_reshard(plan, src, [out[i * S2:(i + 1) * S2] for i in range(w2)], cks)
+    torch.cuda.synchronize()
+    assert torch.equal(out[:n], flat[:n]) and not out[n:].any()
+    want = []
+    for e in range(0, w2 * S2, b // 4):  # sums mod 2^64, as 64-bit integers wrap
+        word = out[e:e + b // 4].to(torch.int64) & 0xFFFFFFFF
+        at = torch.arange(1, word.numel() + 1, device="cuda")
+        want.append(torch.stack([word.sum(), (at * word).sum()]))
+    assert torch.equal(cks, torch.stack(want))
