@@ -2,6 +2,7 @@
 // stand-in runtime of fake_hip.h and plain loops in place of the kernels: what is enqueued, in what
 // order, and what is left behind when a call fails or a plan goes away.
 //   host_check copies|sums|destroy|order
+//   host_check pieces L H Hq Hkv D F V  W T|-W' B depth   (prints how many pieces the call packs)
 // Exit status 0 when everything holds.
 #include "fake_hip.h"
 
@@ -418,6 +419,26 @@ void check_order() {
     }
 }
 
+// The path through host memory over one plan, twice: the pieces of its launches, each reloaded by the
+// launch behind it, put the whole stream and its checksums in place.
+void check_pieces(char** a) {
+  const dr_model m{atoi(a[0]), atoi(a[1]), atoi(a[2]), atoi(a[3]), atoi(a[4]), atoi(a[5]), atoi(a[6])};
+  Work k = setup(m, atoi(a[7]), atoi(a[8]), strtoull(a[9], nullptr, 10), atoi(a[10]));
+  for (int i = 0; i < 2; ++i) {
+    k.clear();
+    launched.clear();
+    CHECK(!k.through_host(k.dst, stream()), "%s", dr_last_error());
+    (void)hipDeviceSynchronize();
+    CHECK(k.right(k.dst), "through host");
+    size_t packs = 0;
+    for (const StageRecord& r : launched) packs += r.relay && r.ntiles;
+    CHECK(launched.size() == packs + 1 && !launched.back().ntiles, "%zu launches", launched.size());
+    if (!i) std::printf("pieces %zu\n", packs);
+  }
+  dr_plan_destroy(k.p);
+  fake::release_for_good();
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -426,6 +447,7 @@ int main(int argc, char** argv) {
   else if (mode == "sums") check_sums();
   else if (mode == "destroy") check_destroy();
   else if (mode == "order") check_order();
+  else if (mode == "pieces" && argc == 13) check_pieces(argv + 2);
   else return 2;
   CHECK(!fake::dead_accesses, "%d accesses to freed memory", fake::dead_accesses);
   std::printf("%s: %d errors\n", mode.c_str(), errors);

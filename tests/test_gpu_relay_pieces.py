@@ -31,15 +31,28 @@ def _out(info):
     return torch.full((info["rollout_bytes"],), 0xFF, dtype=torch.uint8, device="cuda"), new_checksums(info["num_chunks"])
 
 
-# odd widths (pieces end inside unaligned segments) and aligned ones; chunks of one piece, of
-# several, and of 16 MiB exactly (a piece) or one group more
-@pytest.mark.parametrize("model,w,t,b,depth", [
-    ((2, 1024, 6, 3, 72, 3 * 1821, 3 * 401), 5, 3, 1 << 30, 0),
-    ((2, 1024, 6, 3, 72, 3 * 1821, 3 * 401), 5, 3, 40 * MiB + 16, 2),
-    ((2, 1024, 6, 3, 72, 3 * 1821, 3 * 401), 5, 3, 16 * MiB, 4),
-    ((2, 1024, 8, 4, 64, 4096, 4000), 8, 4, 16 * MiB + 16, 0),
-    ((2, 1024, 8, 4, 64, 4096, 4000), 8, 4, 33 * MiB, 0),
-])
+# A chunk is cut into pieces of about 32 MiB, from 48 MiB on (two), 80 MiB on (three).  The numbers of pieces of
+# these calls are checked against the library on the CPU (tests/test_native_host.py).
+ODD, EVEN = (1024, 6, 3, 72, 3 * 1821, 3 * 401), (1024, 8, 4, 64, 4096, 4000)
+
+# odd widths (pieces end inside unaligned segments) and aligned ones; chunks of one piece, of several, and of
+# sizes around one and a half and two and a half pieces, several such chunks in a row
+STAGE_PIECES = [  # model, W, T, B, tile depth, pieces of the whole call
+    ((2,) + ODD, 5, 3, 1 << 30, 0, 3),
+    ((2,) + ODD, 5, 3, 40 * MiB + 16, 2, 2),
+    ((2,) + ODD, 5, 3, 16 * MiB, 4, 5),
+    ((2,) + EVEN, 8, 4, 16 * MiB + 16, 0, 5),
+    ((2,) + EVEN, 8, 4, 33 * MiB, 0, 3),
+    ((6,) + ODD, 5, 3, 48 * MiB + 4096 + 16, 0, 9),
+    ((6,) + ODD, 5, 3, 81 * MiB, 2, 8),
+    ((8,) + EVEN, 8, 4, 47 * MiB, 0, 5),
+    ((8,) + EVEN, 8, 4, 49 * MiB, 0, 9),
+    ((8,) + EVEN, 8, 4, 79 * MiB, 4, 6),
+    ((8,) + EVEN, 8, 4, 81 * MiB, 4, 8),
+]
+
+
+@pytest.mark.parametrize("model,w,t,b,depth", [c[:5] for c in STAGE_PIECES])
 def test_pieces_of_a_chunk(model, w, t, b, depth):
     say("stage_through_host pieces", model, "W", w, "T", t, "B", b, "depth", depth)
     rollout = dr.dr_plan_create_host(model, w, t, b).info["rollout_bytes"]
@@ -53,10 +66,22 @@ def test_pieces_of_a_chunk(model, w, t, b, depth):
         assert torch.equal(dst, want) and torch.equal(cks, want_cks)
 
 
-@pytest.mark.parametrize("w,w2,b", [(5, 3, 64 * MiB), (3, 64, 40 * MiB + 16), (8, 1, 16 * MiB), (1, 7, 16 * MiB + 16),
-                                    (2, 64, 4096)])
-def test_reshard_pieces_across_destination_shards(w, w2, b):
-    model = (1, 512, 4, 4, 64, 2048, 8000) if b > 4096 else (1, 64, 2, 2, 8, 96, 400)
+SMALL, LARGE = (1, 512, 4, 4, 64, 2048, 8000), (2, 1024, 8, 4, 64, 4096, 16000)
+RESHARD_PIECES = [  # model, W, W', B, pieces of the whole call
+    (SMALL, 5, 3, 64 * MiB, 1),
+    (SMALL, 3, 64, 40 * MiB + 16, 2),
+    (SMALL, 8, 1, 16 * MiB, 3),
+    (SMALL, 1, 7, 16 * MiB + 16, 3),
+    ((1, 64, 2, 2, 8, 96, 400), 2, 64, 4096, 80),
+    (LARGE, 5, 3, 64 * MiB + 16, 7),
+    (LARGE, 3, 64, 97 * MiB, 7),
+    (LARGE, 8, 1, 47 * MiB, 5),
+    (LARGE, 1, 7, 1 << 30, 7),
+]
+
+
+@pytest.mark.parametrize("model,w,w2,b", [c[:4] for c in RESHARD_PIECES])
+def test_reshard_pieces_across_destination_shards(model, w, w2, b):
     say("reshard_through_host pieces", model, w, "->", w2, "B", b)
     plan = dr.dr_reshard_plan_create(model, w, w2, b)
     info = dr.dr_plan_get_info(plan)
