@@ -45,6 +45,10 @@ STAGE_PIECES = [  # model, W, T, B, tile depth, pieces of the whole call
     ((2,) + EVEN, 8, 4, 33 * MiB, 0, 3),
     ((6,) + ODD, 5, 3, 48 * MiB + 4096 + 16, 0, 9),
     ((6,) + ODD, 5, 3, 81 * MiB, 2, 8),
+    # many shards: cuts inside the column slices, so that pieces end at any element
+    ((6,) + ODD, 61, 3, 1 << 30, 0, 9),
+    ((6,) + ODD, 64, 3, 48 * MiB + 4096 + 16, 2, 9),
+    ((7,) + ODD, 53, 3, 100 * MiB, 4, 10),
     ((8,) + EVEN, 8, 4, 47 * MiB, 0, 5),
     ((8,) + EVEN, 8, 4, 49 * MiB, 0, 9),
     ((8,) + EVEN, 8, 4, 79 * MiB, 4, 6),
