@@ -44,7 +44,7 @@ def alg_bytes(info) -> int:
 
 
 _COMMON = ("paper_2607_22614_amd/csrc/device_common.h", "paper_2607_22614_amd/csrc/dev_types.h",
-           "paper_2607_22614_amd/csrc/kernels.h")
+           "paper_2607_22614_amd/csrc/kernels.h", "paper_2607_22614_amd/csrc/tile_index.h")
 KERNEL_SOURCES = {"stage_kernel": ("paper_2607_22614_amd/csrc/stage.hip",) + _COMMON,
                   "reshard_kernel": ("paper_2607_22614_amd/csrc/reshard.hip",) + _COMMON,
                   "moment_sum_kernel": ("paper_2607_22614_amd/csrc/moment_sums.hip",) + _COMMON}

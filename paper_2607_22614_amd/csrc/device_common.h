@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "dev_types.h"
+#include "tile_index.h"
 
 namespace dr {
 
@@ -132,25 +133,6 @@ __device__ __forceinline__ void finish_tile_sums(const ChunkSum& cs, uint32_t g,
   a1 = wave_sum_to_lane63(a1);
   a2 = wave_sum_to_lane63(a2);
   if (lane == 63) *reinterpret_cast<u64x2*>(&cs.out[c - cs.out_chunk0]) = (u64x2){a1, a2};
-}
-
-// Tile run by the b-th workgroup: XCD x = b % 8 takes tiles
-// [x*per + min(x, rem), ...) in order, where per/rem split n tiles over 8
-// XCDs.  A bijection on [0, n) for every n.
-__device__ __forceinline__ uint32_t xcd_tile(uint32_t b, uint32_t n) {
-  const uint32_t per = n / kXcds, rem = n % kXcds, x = b % kXcds;
-  return x * per + min(x, rem) + b / kXcds;
-}
-
-// Item run by the b-th workgroup in grouped order: the XCDs take groups of G consecutive items in
-// turn, so the chip works on one window of 8*G items; the last n % (8*G) items in plain order.  A
-// bijection on [0, n) for every n; item b of a full window runs on XCD b % 8.
-template <uint32_t G, typename T>
-__device__ __forceinline__ T xcd_group(T b, T n) {
-  static_assert((G & (G - 1)) == 0, "power of two");
-  if (b >= (n & ~(T)(kXcds * G - 1))) return b;
-  const T x = b % kXcds, i = b / kXcds;
-  return (i / G * kXcds + x) * G + i % G;
 }
 
 }  // namespace dr

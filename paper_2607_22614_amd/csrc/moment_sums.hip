@@ -27,7 +27,6 @@
 namespace dr {
 namespace {
 
-constexpr uint32_t kTileGroup = 64;  // tiles of a group in grouped order
 constexpr int kPieces = 2 * DR_MAX_SHARDS;  // m_0..m_{W-1}, v_0..v_{W-1}
 
 struct MomentArgs {

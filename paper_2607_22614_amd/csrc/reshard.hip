@@ -16,12 +16,6 @@
 namespace dr {
 namespace {
 
-// A workgroup's part of a tile (groups per lane), and the parts of a group in grouped order.
-constexpr int kPartIters = 2;
-constexpr uint32_t kPartGroup = 32;
-constexpr uint32_t kTileParts = kReshardIters / kPartIters;
-static_assert(kTileParts == 2, "a tile is two parts");
-
 struct ReshardArgs {
   const DevSeg* segs;
   const Tile* tiles;
@@ -187,8 +181,7 @@ hipError_t launch_reshard_kernel(const ReshardLaunch& l, hipStream_t st) {
     hipLaunchKernelGGL(reshard_kernel<false>, dim3(std::min(l.ntiles, kMaxGrid)), dim3(kThreads), 0, st, args);
     return hipGetLastError();
   }
-  // one part where a chunk, and so a tile, holds no more groups than a part
-  args.part_shift = l.chunk_elems / 4 <= (uint64_t)kPartIters * kThreads ? 0 : 1;
+  args.part_shift = reshard_part_shift(l.chunk_elems);
   const uint64_t grid = std::min<uint64_t>((uint64_t)l.ntiles << args.part_shift, kMaxGrid);
   hipLaunchKernelGGL(reshard_kernel<true>, dim3((uint32_t)grid), dim3(kThreads), 0, st, args);
   return hipGetLastError();

@@ -48,8 +48,6 @@
 namespace dr {
 namespace {
 
-constexpr uint32_t kTileGroup = 64;  // tiles of a group in grouped order
-
 // Everything a stage launch needs, passed as the kernel's only argument.  The
 // kernel reads it through the kernarg segment pointer, so the shard table is
 // indexed with one scalar load instead of being copied into registers.
@@ -86,19 +84,6 @@ __device__ __forceinline__ uint32_t cvt_pk_bf16(float x, float y) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){x, y}, bf16x2));
 }
 
-// q = e / cols, r = e % cols for e < 2^32, from magic = floor(2^32 / cols):
-// the estimate is at most one below the quotient, so one correction suffices.
-__device__ __forceinline__ uint32_t div_cols(uint32_t e, uint32_t cols, uint32_t magic, uint32_t* rem) {
-  uint32_t q = __umulhi(e, magic);
-  uint32_t r = e - q * cols;
-  if (r >= cols) {
-    q += 1;
-    r -= cols;
-  }
-  *rem = r;
-  return q;
-}
-
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 constexpr int kGroups = kScalarIters / 4;  // groups of 4 elements per lane in an unaligned tile
 static_assert(kScalarIters % 4 == 0, "unaligned tiles are whole groups per lane");
@@ -109,28 +94,24 @@ struct Group {
   uint32_t cut;
 };
 
-// Loads elements [e, e+4) of an unaligned segment, 0 for those outside [0, units).  A group inside
-// the segment takes one 16-byte load at a 4-byte boundary; if its row ends inside it, a second
-// one brings the rest from the next row (both lie between the group's first and last source
-// element: the row after the cut belongs to the segment).  The segment's ends and rows shorter
-// than a group are loaded element by element, so nothing outside the segment's span is read.
+// Loads elements [e, e+4) of an unaligned segment, 0 for those outside [0, units): with one or two
+// 16-byte loads at 4-byte boundaries (wide_group), the segment's ends and rows shorter than a
+// group element by element, so nothing outside the segment's span is read.
 __device__ __forceinline__ void load_group(const float* __restrict__ src, const DevSeg& s, int32_t e, Group& g) {
-  uint32_t col = (uint32_t)e, row = 0;
-  if (s.rows > 1) row = div_cols((uint32_t)max(e, 0), s.cols, s.magic, &col);
+  uint32_t col;
+  const uint32_t so = elem_src(s, (uint32_t)max(e, 0), &col);
   g.a = g.b = (f32x4){0.f, 0.f, 0.f, 0.f};
   g.cut = 4;
-  if (e >= 0 && (uint32_t)e + 4 <= s.units && s.cols >= 4) {
-    const float* p = src + row * s.stride + col;
+  if (wide_group(s, e)) {
+    const float* p = src + so;
     g.a = __builtin_nontemporal_load(reinterpret_cast<const f32x4u*>(p));
-    g.cut = min(s.cols - col, 4u);
+    g.cut = group_cut(s, col);
     if (g.cut < 4) g.b = __builtin_nontemporal_load(reinterpret_cast<const f32x4u*>(p + (s.stride - s.cols)));
   } else {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       if (e + j < 0 || (uint32_t)(e + j) >= s.units) continue;
-      uint32_t c = (uint32_t)(e + j), r = 0;
-      if (s.rows > 1) r = div_cols((uint32_t)(e + j), s.cols, s.magic, &c);
-      g.a[j] = load_stream(src + r * s.stride + c);
+      g.a[j] = load_stream(src + elem_src(s, (uint32_t)(e + j), &col));
     }
   }
 }
@@ -186,19 +167,16 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, uint32_t g, uint6
     }
   } else {
     // Unaligned segment (a source offset, destination offset or row that is no whole group of 4
-    // elements).  The tiles still move groups of 4 elements, laid on the destination's 8-byte
-    // grid: group g of the segment holds its elements [4g - lead, 4g - lead + 4), so the
-    // first and the last group can be partial and a row can end inside a group.
+    // elements): groups of 4 elements on the destination's 8-byte grid (tile_index.h).
     Group v[kGroups];
 #pragma unroll
     for (int k = 0; k < kGroups; ++k) {
-      const int32_t e = (int32_t)(tile.unit0 + 4 * (k * kThreads + threadIdx.x)) - (int32_t)lead;
+      const int32_t e = group_elem(tile.unit0, k, threadIdx.x, lead);
       load_group(src, s, e, v[k]);
     }
 #pragma unroll
     for (int k = 0; k < kGroups; ++k) {
-      const uint32_t g4 = tile.unit0 + 4 * (k * kThreads + threadIdx.x);  // 4 * group
-      const int32_t e = (int32_t)g4 - (int32_t)lead;
+      const int32_t e = group_elem(tile.unit0, k, threadIdx.x, lead);
       f32x4 x = v[k].a;
       if (v[k].cut < 4) {
 #pragma unroll
@@ -206,7 +184,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, uint32_t g, uint6
       }
       const uint32_t w0 = cvt_pk_bf16(x.x, x.y);
       const uint32_t w1 = cvt_pk_bf16(x.z, x.w);
-      if (e >= 0 && (uint32_t)e + 4 <= s.units) {
+      if (whole_group(s, e)) {
         store_stream((u32x2){w0, w1}, reinterpret_cast<u32x2*>(out + e));
       } else {
         const uint16_t h[4] = {(uint16_t)w0, (uint16_t)(w0 >> 16), (uint16_t)w1, (uint16_t)(w1 >> 16)};
@@ -215,17 +193,15 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, uint32_t g, uint6
           if (e + j >= 0 && (uint32_t)(e + j) < s.units) out[e + j] = h[j];
       }
       // elements outside the segment were loaded as 0 and add nothing to either sum
-      const uint32_t rel = g4 >> 1;
+      const uint32_t rel = (uint32_t)(e + (int32_t)lead) >> 1;
       acc_w += (uint64_t)w0 + w1;
       acc_rw += (uint64_t)rel * w0 + (uint64_t)(rel + 1) * w1;
     }
-    // The groups of a segment's last tile end `lead` elements before the tile's last unit: up to
-    // three more elements, one lane each.
-    const uint32_t x = tile.unit0 + kScalarUnitsPerTile - lead + threadIdx.x;
-    if (threadIdx.x < lead && tile.unit0 + kScalarUnitsPerTile >= s.units && x < s.units) {
-      uint32_t col = x, row = 0;
-      if (s.rows > 1) row = div_cols(x, s.cols, s.magic, &col);
-      const uint32_t bf = cvt_pk_bf16(load_stream(src + row * s.stride + col), 0.f) & 0xFFFFu;
+    uint32_t x;
+    if (tail_elem(s, tile.unit0, threadIdx.x, lead, &x)) {
+      uint32_t col;
+      const uint32_t so = elem_src(s, x, &col);
+      const uint32_t bf = cvt_pk_bf16(load_stream(src + so), 0.f) & 0xFFFFu;
       out[x] = (uint16_t)bf;
       const uint32_t q = lead + x;  // element position relative to the first group
       const uint32_t val = bf << ((q & 1) * 16);

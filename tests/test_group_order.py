@@ -1,31 +1,21 @@
-"""The grouped order of the tile kernels, on the CPU: a permutation of [0, n) for every n, groups whole on one XCD."""
-import numpy as np
+"""The order in which the tile kernels' workgroups take tiles, and a reshard's parts of a tile, on the CPU: the
+compiled index functions of the kernels (csrc/tile_index.h) over counts around their windows."""
 import pytest
 
-XCDS = 8  # dev_types.h kXcds
+from tests.native_build import MISSING, native, run
+
+pytestmark = pytest.mark.skipif(MISSING, reason="g++ or the HIP headers not available")
 
 
-def _xcd_group(b, n, G):
-    if b >= (n & ~(XCDS * G - 1)):
-        return b
-    x, i = b % XCDS, b // XCDS
-    return (i // G * XCDS + x) * G + i % G
+@pytest.fixture(scope="module")
+def index_check(tmp_path_factory):
+    return native(str(tmp_path_factory.mktemp("index") / "index_check"), "index_check.cpp")
 
 
-@pytest.mark.parametrize("G", [32, 64])  # kPartGroup (reshard.hip), kTileGroup (stage.hip, moment_sums.hip)
-@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 511, 512, 513, 1023, 1024, 1025, 1536, 4099, 8192, 10000])
-def test_grouped_order_is_a_permutation(n, G):
-    t = np.array([_xcd_group(b, n, G) for b in range(n)])
-    assert np.array_equal(np.sort(t), np.arange(n))
-    full = n & ~(XCDS * G - 1)
-    for g in range(full // G):  # the workgroups of a group share an XCD
-        assert len({b % XCDS for b in np.flatnonzero(t // G == g) if b < full}) == 1
-
-
-@pytest.mark.parametrize("groups", [1, 255, 511, 512, 513, 1023, 1024, 5000])
-def test_reshard_parts_cover_a_tile(groups):
-    """reshard_kernel moves a tile in one part of 512 groups where a chunk holds no more, else in two:
-    the largest tile (at most a chunk, at most 1024 groups) is covered, and no part of it is empty."""
-    parts = 1 if groups <= 512 else 2
-    tile = min(groups, 1024)
-    assert parts * 512 >= tile > (parts - 1) * 512
+@pytest.mark.parametrize("what", [
+    "order",  # grouped and contiguous order are permutations, groups whole on one XCD
+    "division",  # a row's division and an element's source offset
+    "parts",  # parts cover every group of every segment once
+])
+def test_index_functions(index_check, what):
+    run(index_check, what)
