@@ -88,6 +88,15 @@ typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 constexpr int kGroups = kScalarIters / 4;  // groups of 4 elements per lane in an unaligned tile
 static_assert(kScalarIters % 4 == 0, "unaligned tiles are whole groups per lane");
 
+// load_stream of 4 elements at a 4-byte boundary (a template argument would lose the alignment).
+__device__ __forceinline__ f32x4 load_stream4u(const float* p) {
+#if DR_NT_LOADS
+  return __builtin_nontemporal_load(reinterpret_cast<const f32x4u*>(p));
+#else
+  return *reinterpret_cast<const f32x4u*>(p);
+#endif
+}
+
 // A group of an unaligned segment on its way: element j comes from a if j < cut, else from b.
 struct Group {
   f32x4 a, b;
@@ -104,9 +113,9 @@ __device__ __forceinline__ void load_group(const float* __restrict__ src, const 
   g.cut = 4;
   if (wide_group(s, e)) {
     const float* p = src + so;
-    g.a = __builtin_nontemporal_load(reinterpret_cast<const f32x4u*>(p));
+    g.a = load_stream4u(p);
     g.cut = group_cut(s, col);
-    if (g.cut < 4) g.b = __builtin_nontemporal_load(reinterpret_cast<const f32x4u*>(p + (s.stride - s.cols)));
+    if (g.cut < 4) g.b = load_stream4u(p + (s.stride - s.cols));
   } else {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {

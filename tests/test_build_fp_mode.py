@@ -50,3 +50,13 @@ def test_kernels_preserve_fp32_denormals(src):
     assert kernels and len(modes) == len(kernels)
     # 3: denormal inputs and outputs both preserved (no flush)
     assert set(modes) == {"3"}, dict(zip(kernels, modes))
+
+
+@needs_hipcc
+@pytest.mark.parametrize("src", ["stage.hip", "reshard.hip", "moment_sums.hip"])
+def test_the_nontemporal_switches_reach_every_access(src):
+    hinted = r"^\s*global_(?:load|store)\S*\s.*\bnt\b"
+    on, off = _device_asm(src), _device_asm(src, ["-DDR_NT_LOADS=0", "-DDR_NT_STORES=0"])
+    assert on.returncode == 0 and off.returncode == 0, on.stderr + off.stderr
+    assert re.search(hinted, on.stdout, re.M)
+    assert not re.findall(hinted, off.stdout, re.M)
