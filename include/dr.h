@@ -257,6 +257,11 @@ int dr_plan_segment(const dr_plan* plan, uint64_t index, dr_segment* out);
  *              are valid once the stream has reached this point.
  * Two calls in flight at once on one plan must not cover the same chunk
  * (they share that chunk's checksum accumulators in the plan).
+ * The call enqueues the stage kernel and a small kernel that writes the
+ * checksums.  Launches of at most 2048 tiles outside a graph, with 9 to 128
+ * tiles in the plan's largest chunk, write them in the stage kernel itself.
+ * A call that failed behind its first launch leaves the buffers given to it
+ * undefined and the later calls' results right.
  * Graphs: the call only enqueues kernels (no memset, allocation or host
  * synchronization), so it may be recorded into a HIP graph; the recorded
  * launches keep the pointers given here and the plan's device tables, so
@@ -273,8 +278,8 @@ int dr_stage_chunk(dr_plan* plan, uint64_t chunk, const float* const* shards, vo
  * the same kernels, but the chunk's checksum accumulators live in a fixed
  * static device array of the library (32 KiB per GPU, kept until the process
  * ends) instead of the plan's.  The call allocates nothing (no hipMalloc, no
- * allocating library call); it launches the stage kernel and, but for small
- * chunks outside a graph, the chunk-sum kernel.  The first call on a GPU clears
+ * allocating library call); it launches the stage kernel and, unless that one
+ * sums the chunk (see dr_stage_chunk), the chunk-sum kernel.  The first call on a GPU clears
  * the array with a small kernel first, and every call leaves it at zero (what
  * sums the slots clears them);
  * after a call that failed, the following calls clear it first again, up to

@@ -10,10 +10,11 @@
 namespace dr {
 
 // Launch geometry of the kernels.  A workgroup of kThreads lanes handles one
-// tile: K groups of 4 elements per lane on aligned segments, or kScalarIters
-// single elements per lane on unaligned ones.  The stage kernel runs at tile
-// depth K = kVecItersSmall or kVecItersLarge (the host picks per plan and per
-// launch); the reshard kernel at K = kReshardIters.
+// tile: K groups of 4 elements per lane on aligned segments, or kScalarIters/4
+// groups per lane on unaligned ones.  The stage kernel runs at tile depth
+// K = kVecItersSmall or kVecItersLarge (the host picks per plan and per launch);
+// the tiles of reshards and of the moment stream have K = kReshardIters, and a
+// workgroup of a reshard moves a whole tile or half of one (reshard.hip).
 // Stage grid: 0 launches one workgroup per tile (at most kMaxGrid, which then
 // stride over the tiles); N > 0 caps the grid at N workgroups.
 #ifndef DR_GRID_CAP
@@ -76,16 +77,18 @@ struct Tile {
 };
 
 // Per-chunk checksums.  Each tile adds its (s1, s2) with two atomic adds
-// (nothing waits for them) into one of `sub` accumulator slots of its chunk,
-// slot g % sub for tile g; a small kernel that runs after the tile kernel adds
-// a chunk's slots, writes the checksum and sets the slots back to zero, so
-// they are zero between launches.  Slots of chunk c start at slot
+// (nothing waits for them; a reshard in half tiles adds once for each half) into
+// one of `sub` accumulator slots of its chunk, slot g % sub for tile g; a small
+// kernel that runs after the tile kernel adds a chunk's slots, writes the
+// checksum and sets the slots back to zero, so they are zero between launches
+// (but for launches that failed: clear_sums).  Slots of chunk c start at slot
 // (c - chunk_bias) * sub and lie stride_words 64-bit words apart.  How many
 // slots, and how far apart, is the host's choice (a plan's tiling): adds to
 // one cache line are performed one after another, so the slots spread the
 // adds of a chunk's concurrent tiles over lines.
-// A small launch sums its chunks itself instead (ChunkSum::chunk_tiles set): behind its adds each
-// tile takes a ticket of its chunk, and the one with the last ticket does the small kernel's work.
+// A small stage launch sums its chunks itself instead (ChunkSum::chunk_tiles set): each tile waits for
+// its adds, then takes a ticket of its chunk, and the one with the last ticket does the small kernel's
+// work; no kernel follows.
 constexpr uint32_t kMaxSumSlots = 256;
 constexpr uint32_t kSlotLineWords = 16;  // 128-byte line
 constexpr uint32_t kTicketWord = 2;      // of a chunk's first slot, where slots lie a line apart

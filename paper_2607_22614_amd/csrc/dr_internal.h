@@ -55,6 +55,7 @@ inline bool pack_is_hot(int64_t now, int64_t prev_drain) {
 // chunk up to that many tiles, then a power of two of slots (at most kMaxSumSlots), one line each.
 // Chunks of at most kPackedSlotTiles tiles pack their single slots 16 bytes apart, 8 chunks to a
 // line (at most 64 tiles' adds per line), which keeps a million tiny chunks' accumulators small.
+// A reshard in half tiles adds twice per tile, so a line of its slots takes up to 64 adds (packed: 128).
 // Measured on the 8B workload at tile depth 2: 256 KiB chunks (64 tiles) with packed single slots,
 // 1024 adds per line in a burst, took the stage kernel from 7.3 to 10.6 ms (7.5 ms with two slots
 // a line each); 16 KiB chunks (4-5 tiles) took 8.1 ms with a line per chunk against 7.7 packed.
@@ -75,8 +76,14 @@ inline uint32_t sum_stride(uint32_t slots, uint32_t max_chunk_tiles) {
 // host 2.7 us.  Through the binding, tiny workload: 13.3 -> 10.1 us a pack, 13.3 -> 10.0 a chunk call.
 // Replayed from a graph only the device counts, where the two are alike up to 64 tiles a chunk (4.3 us
 // against 4.5-4.6 for a 256 KiB chunk) and the tickets of a chunk, taken one after another, cost more
-// than the kernel beyond (1 MiB, 128 tiles: 5.6 against 4.9; 4 MiB: 10.7 against 6.0).  2048: the
-// workgroups that the 256 CUs hold at once; a waiting one would keep others from starting.
+// than the kernel beyond (1 MiB, 128 tiles: 5.6 against 4.9; 4 MiB: 10.7 against 6.0).  A tile that waits
+// for its adds holds its place on the chip, so the gain shrinks with the tiles of a launch: packs
+// back to back in us, the kernel behind / own sums, chunks of 16-128 tiles: 250-1000 tiles 10.0-10.6 /
+// 6.4-6.7, 1500 9.8-11.0 / 6.5-7.3, 2000 9.9-11.4 / 7.2-8.1, 2600 10.0-12.5 / 8.0-9.2, 4000 11.1-11.6 /
+// 10.6-11.8, 6000 14.9-15.4 / 14.6-16.4, 8000 19.0 / 18.8-20.1; after idle time the two are alike.  2048 lies
+// well on the gaining side of the crossing at about 4000.
+// Chunks of at most kPackedSlotTiles tiles have no line each for a ticket: they keep the kernel, as do
+// dr_reshard and dr_moment_checksums at every size.
 constexpr uint32_t kOwnSumTiles = 2048;
 constexpr uint32_t kOwnSumChunkTiles = 128;
 

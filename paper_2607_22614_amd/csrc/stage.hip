@@ -28,15 +28,17 @@
 //   * XCD-aware tile order: the hardware hands workgroup b to XCD b % 8, and
 //     the kernel maps it to a tile so that each XCD streams through one
 //     contiguous eighth of the stream instead of every eighth tile (measured
-//     faster on the 8B shape: 6.3 vs 6.0 TB/s), or, in short launches, so that
-//     the XCDs take groups of 64 tiles in turn (StageLaunch::grouped);
+//     faster on the 8B shape: 6.3 vs 6.0 TB/s), or, in launches of up to a few
+//     GiB, so that the XCDs take groups of 64 tiles in turn
+//     (StageLaunch::grouped);
 //   * the chunk checksum is accumulated from the packed words while they are
 //     in registers, reduced across the wavefront (DPP moves, no LDS) and the
 //     workgroup (LDS), and added with two 64-bit atomic adds (nothing waits
 //     for them) into one of the chunk's accumulator slots; a small kernel
-//     behind the launch adds a chunk's slots.  The sums are integer, so the
-//     bits do not depend on the order of the adds, and there is no extra
-//     pass over the data.
+//     behind the launch adds a chunk's slots.  In small launches each tile
+//     waits for its adds and the last one of a chunk adds the slots, with no
+//     kernel behind.  The sums are integer, so the bits do not depend on the
+//     order of the adds, and there is no extra pass over the data.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -233,7 +235,8 @@ __global__ __launch_bounds__(kThreads) void stage_kernel(StageArgs args) {
   (void)args;  // read below through the kernarg segment (same bytes)
   const StageArgs& a = *(const StageArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   __shared__ uint64_t red[2][kThreads / 64];
-  // the grid holds at most ntiles workgroups: the first tile needs no check, so its arguments load at once
+  // The grid holds at most ntiles workgroups: the first tile needs no check, so its arguments load at once.
+  // 50 tiny packs replayed from a graph 6.49 us each against 6.58 with the check, 0.5B 568.9 against 570.3.
   uint32_t b = blockIdx.x;
   do {
     const uint32_t t = a.grouped ? xcd_group<kTileGroup>(b, a.ntiles) : xcd_tile(b, a.ntiles);
