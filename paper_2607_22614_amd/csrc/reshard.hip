@@ -78,13 +78,14 @@ __device__ __forceinline__ void reshard_tile(const ReshardArgs& a, uint32_t g, u
 // halves (256 KiB) in turn; else it moves a whole tile and each XCD streams through one eighth.
 // Bound by HBM, where the read and the write stream meet in the same banks: how they fall together
 // depends on the tile's size, on the order and on where the buffers lie.  Mean over five placements
-// of the buffers (+- over the placements) in us, whole / halves, back to back; after 30 ms idle:
+// of the buffers (24, 32 and 44 layers 8 to 6: fourteen) with their standard deviation, in us, whole /
+// halves, back to back; after 30 ms idle:
 //   0.5B, 8 to 6 shards (5.0 GB)  825+-18 / 790+-3; 861 / 825      odd width, 5 to 3 (5.4)  943+-4 / 877+-15; 975 / 910
 //   8B width, 8 layers, 4 to 16 (22.3)  3651+-16 / 3560+-47; 3678 / 3605
 //   16 layers, 8 to 6 (36.3)  5811+-158 / 5650+-55; 5894 / 5816    20 (43.3)  6882+-230 / 6764+-29; 6931 / 6849
-//   24 layers (50.3)  7818+-158 / 7858+-39; 7876 / 7954            28 (57.2)  8817+-118 / 8946+-30; 8902 / 9056
-//   32 layers (64.2)  9964+-226 / 10090+-19; 10009 / 10223         32, 8 to 3  10094 / 10076; 10186 / 10200
-//   32, 4 to 16  10036 / 10029; 10076 / 10145                      44 (85)  13211+-86 / 13348+-65; 13273 / 13494
+//   24 layers (50.3)  7793+-73 / 7860+-48; 7839 / 7963             28 (57.2)  8817+-118 / 8946+-30; 8902 / 9056
+//   32 layers (64.2)  9962+-328 / 10045+-64; 10008 / 10142         32, 8 to 3  10094 / 10076; 10186 / 10200
+//   32, 4 to 16  10036 / 10029; 10076 / 10145                      44 (85)  13248+-70 / 13358+-86; 13285 / 13497
 //   32B width, 20 layers (91)  14130 / 14185; 14177 / 14350
 // So halves up to kWholeTileBytes, whole tiles beyond (launch_reshard).  Halves in groups of 16 / 64 /
 // 128 instead of 32 at 16 layers: 5882 / 5700 / 5655, at 32 layers 10602 / 10169 / 10180; halves in
