@@ -35,13 +35,13 @@ int check_device(const dr_plan* p, const char* what) {
 // tiles, in contiguous order on eight places of the stream at once.  Once the launch runs, contiguous
 // order is the faster one.  The line depends on the depth, not on what ran before the launch or
 // which call makes it.  Grouped against contiguous, back to back / after 30 ms idle, GiB read and
-// written, decoders of six widths:
-//   depth 2, whole streams: 0.3-0.9 -1..-5 % / -0..-3; 1.2-2.5 -0..-4 / +1..-3; 3.5-4.5 +0..-3 / +1..-3;
-//   5-5.5 +1..-3 / +2..-3; 6.5 +1..-2; 16-45 +2 / +1;
-//   depth 4, whole streams: 0.3-0.5 -2..-4 %; 0.8-2.3 0..-2; 3.9-6.6 -0..-2 / -0..-2 in twelve of
-//   thirteen; 7-8 0; 11-16 +1; 45 +1.5 / +1.5;
+// written, decoders of twelve widths and shard counts:
+//   depth 2: 0.3-0.9 +0.4..-5 %; 1.1-1.8 +1..-4 / +3..-4; 2.2-2.7 +0.3..-3 / +1..-2; 3.3-4.7 +3..-3 / +3..-3;
+//   5-6.7 +4..-3 / +4..-3; 7-16 +0.4..+2; 45 +1.8 / +1.3: by width from 1 GiB on, mostly a loss from 3;
+//   depth 4: 0.3-0.9 0..-6 % / 0..-6; 1-2.7 +0.8..-4 / +2..-5; 3.3-4.7 +2..-3 / +2..-2; 5-6.7 +2..-2 / +2..-2
+//   (a loss at one width only, from 1.6 GiB on); 7-8 0; 11-16 +0.4..+1.1; 45 +1.5 / +1.3;
 //   depth 4, one chunk a launch: 0.2 -8 %, 0.8 -1.4, 3 -2, 6 -1.2, 12 +0.4, 24 +1.1, 45 +1.5 / +1.2.
-constexpr uint64_t kGroupedBytes = 3ull << 30;
+constexpr uint64_t kGroupedBytes = 1ull << 30;
 constexpr uint64_t kGroupedDeepBytes = 6ull << 30;
 
 bool grouped_order(int depth, uint64_t bytes) {

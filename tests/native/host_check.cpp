@@ -375,11 +375,11 @@ void check_destroy() {
   }
 }
 
-// The tile order follows a launch's depth and traffic, whichever call makes it: grouped up to 3 GiB
+// The tile order follows a launch's depth and traffic, whichever call makes it: grouped up to 1 GiB
 // at depth 2 and up to 6 GiB at depth 4.  The launches are only recorded, nothing runs.
 void check_order() {
   const struct { int32_t vocab; double gib; } sizes[] = {  // one chunk; GiB read and written
-      {2000, 0.1}, {20000, 0.9}, {60000, 2.7}, {80000, 3.7}, {120000, 5.5}, {140000, 6.5}, {200000, 9.2}};
+      {2000, 0.1}, {20000, 0.9}, {25000, 1.2}, {80000, 3.7}, {120000, 5.5}, {140000, 6.5}, {200000, 9.2}};
   for (const auto& z : sizes)
     for (int depth : {0, 2, 4}) {
       const dr_model m{0, 4096, 32, 8, 128, 14336, z.vocab};
@@ -396,7 +396,7 @@ void check_order() {
         CHECK(!rc && launched.size() == 1, "%s", dr_last_error());
         const StageRecord& r = launched.back();
         CHECK(!depth || r.depth == depth, "depth %d", r.depth);
-        CHECK(r.grouped == (z.gib < (r.depth == 4 ? 6 : 3)), "%.1f GiB, depth %d, chunk call %d: grouped %d", z.gib, r.depth,
+        CHECK(r.grouped == (z.gib < (r.depth == 4 ? 6 : 1)), "%.1f GiB, depth %d, chunk call %d: grouped %d", z.gib, r.depth,
               chunk, r.grouped);
       }
       fake::null_stream.ops.clear();
