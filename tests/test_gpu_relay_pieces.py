@@ -1,5 +1,7 @@
 """The path through host memory where its launches meet: chunks of several pieces, pieces that end inside unaligned
 column slices, reloads across destination shards, destinations reloaded by copies, calls in order on two streams."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -141,6 +143,27 @@ def test_calls_on_two_streams_of_one_plan_are_ordered():
     torch.cuda.synchronize()
     for i, (d, c) in enumerate(outs):
         assert torch.equal(d, want[i % 2][0]) and torch.equal(c, want[i % 2][1]), i
+
+
+def test_a_stream_that_is_gone_when_the_plan_is_used_again():
+    """The plan orders its calls by an event recorded on the caller's stream, which may be destroyed by then."""
+    wl = workloads.TINY
+    plan, info, shards, flat = _stage_setup(wl.model, wl.train_shards, wl.tp, wl.chunk_bytes)
+    want, want_cks = _out(info)
+    dr.dr_stage_all(plan, shards, want, want_cks)
+    torch.cuda.synchronize()
+    hip = dr._lib  # the HIP runtime is among the library's dependencies
+    for i in range(3):
+        st = ctypes.c_void_p()
+        assert hip.hipStreamCreateWithFlags(ctypes.byref(st), ctypes.c_uint(1)) == 0  # non-blocking
+        dst, cks = _out(info)
+        torch.cuda.synchronize()
+        say("relay on a stream that is then destroyed", i)
+        dr.dr_stage_through_host(plan, shards, dst, cks, stream=st.value)
+        assert hip.hipStreamSynchronize(st) == 0
+        assert hip.hipStreamDestroy(st) == 0
+        assert torch.equal(dst, want) and torch.equal(cks, want_cks)
+    plan.close()
 
 
 def test_refused_while_the_stream_is_captured():
